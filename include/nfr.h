@@ -201,7 +201,7 @@ size_t nfr_problem_bytes(int64_t n);
  * freed once it has run.  The handle (host memory) references pack_dev, which
  * must stay allocated until nfr_problem_destroy.  The pack also holds a tile
  * order of the nodes (recursive bisection along each segment's longest axis
- * down to blocks of 16 nodes, built on the device by bitonic sorts), in which
+ * down to blocks of 16 nodes, built on the device by median selection), in which
  * the fused BF16 form runs so that blocks of nearby nodes can skip the steep
  * exponential; every call still takes and returns states in the caller's
  * node order. */

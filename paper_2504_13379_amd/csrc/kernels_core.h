@@ -19,11 +19,13 @@ namespace nfr {
 // period/2] (the same points of the periodic plane).  The fourth component is
 // the squared norm of the FP32 coordinates, rounded once from FP64 (0 with
 // period > 0), for kernels that expand r^2 = |x_i|^2 + |x_j|^2 - 2 x_i . x_j.
+// blockmax[2 b], [2 b + 1]: the workgroup's max |q_j| and max |x_j|^2 (k_qmax).
 __global__ __launch_bounds__(kWG) void k_pack(const double* __restrict__ xyz, const double* __restrict__ q,
                                               int64_t n, int64_t npad, double period, float4* __restrict__ src,
-                                              double* __restrict__ qd, double* __restrict__ xyz64) {
-  const int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x;
-  if (i >= npad) return;
+                                              double* __restrict__ qd, double* __restrict__ xyz64,
+                                              double* __restrict__ blockmax) {
+  __shared__ double red[2][kWG / 64];
+  const int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x;   // npad is a multiple of kWG
   double x = 0.0, y = 0.0, z = 0.0, w = 0.0;
   if (i < n) {
     x = xyz[3 * i + 0];
@@ -42,17 +44,33 @@ __global__ __launch_bounds__(kWG) void k_pack(const double* __restrict__ xyz, co
   xyz64[3 * i + 0] = x;
   xyz64[3 * i + 1] = y;
   xyz64[3 * i + 2] = z;
+  double m = fmax(0.0, fabs(w)), r = fmax(0.0, (double)(float)nrm);   // fmax drops a NaN
+  for (int off = 32; off > 0; off >>= 1) {
+    m = fmax(m, __shfl_xor(m, off));
+    r = fmax(r, __shfl_xor(r, off));
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[0][threadIdx.x >> 6] = m;
+    red[1][threadIdx.x >> 6] = r;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    double v = red[threadIdx.x][0];
+    for (int wv = 1; wv < kWG / 64; ++wv) v = fmax(v, red[threadIdx.x][wv]);
+    blockmax[2 * (int64_t)blockIdx.x + threadIdx.x] = v;
+  }
 }
 
-// qmax[0] = max_j |q_j| and qmax[1] = max_j |x_j|^2 (the packed FP32 norms) over
-// the npad packed nodes (one workgroup).
-__global__ __launch_bounds__(kWG) void k_qmax(const double* __restrict__ qd, const float4* __restrict__ src, int64_t npad,
+// qmax[0] = max_j |q_j| and qmax[1] = max_j |x_j|^2 (the packed FP32 norms) from
+// the nblocks workgroups' maxima of k_pack (one workgroup).  Over the nodes
+// themselves one workgroup took 76 us at N = 65536, latency-bound.
+__global__ __launch_bounds__(kWG) void k_qmax(const double* __restrict__ blockmax, int64_t nblocks,
                                               double* __restrict__ qmax) {
   __shared__ double red[2][kWG];
   double m = 0.0, r = 0.0;
-  for (int64_t j = threadIdx.x; j < npad; j += kWG) {
-    m = fmax(m, fabs(qd[j]));
-    r = fmax(r, (double)src[j].w);
+  for (int64_t j = threadIdx.x; j < nblocks; j += kWG) {
+    m = fmax(m, blockmax[2 * j]);
+    r = fmax(r, blockmax[2 * j + 1]);
   }
   red[0][threadIdx.x] = m;
   red[1][threadIdx.x] = r;

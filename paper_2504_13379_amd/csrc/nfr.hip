@@ -93,7 +93,7 @@ int fail(int code, const char* fmt, ...) {
 constexpr int64_t kMaxN = 4000000;   // keeps every grid dimension below 65536 blocks
 constexpr int kMaxB = 4096;
 // node indices and segment counts fit the tile order's sort keys (kernels_tile.h)
-static_assert(kMaxN <= (int64_t(1) << kTileNodeBits) && kMaxN / kTileLeaf < (int64_t(1) << kTileSegBits), "tile keys");
+static_assert(kMaxN <= (int64_t(1) << kTileNodeBits), "tile keys");
 
 bool is_finite_d(double x) { return std::isfinite(x); }
 
@@ -688,10 +688,10 @@ int check_w(const nfr_problem* p, int form, const void* w_dev) {
 namespace {
 // Regions of a problem's pack buffer, in order: packed coordinates, weights,
 // FP64 coordinates, the two maxima, then the tile order (kernels_tile.h):
-// slot -> node, coordinates and weights in slot order, block bounds, the
-// bounding box and the sort keys (used while the problem is created).
+// slot -> node, coordinates and weights in slot order, block bounds, and the
+// scratch of the problem's creation (block maxima, then selection keys).
 struct PackLayout {
-  size_t src, q, xyz, qmax, perm, src_t, q_t, bnd32, bnd16, box, keys, bytes;
+  size_t src, q, xyz, qmax, perm, src_t, q_t, bnd32, bnd16, keys, bytes;
 };
 PackLayout pack_layout(int64_t n) {
   const int64_t npad = round_up(n, kPad);
@@ -711,8 +711,7 @@ PackLayout pack_layout(int64_t n) {
   L.q_t = take(npad * sizeof(double));
   L.bnd32 = take(npad / kTileRowBlock * sizeof(float4));
   L.bnd16 = take(npad / kTileColBlock * sizeof(float4));
-  L.box = take(size_t(6) * (size_t(1) << tile_levels(n)) * sizeof(double));   // one box per segment
-  L.keys = take(tile_pow2(npad) * sizeof(uint64_t));
+  L.keys = take(npad * sizeof(uint64_t));
   L.bytes = off;
   return L;
 }
@@ -907,7 +906,6 @@ int nfr_problem_create_periodic(nfr_context* ctx, int64_t n, const double* xyz_d
   double* q_t = reinterpret_cast<double*>(base + L.q_t);
   float4* bnd32 = reinterpret_cast<float4*>(base + L.bnd32);
   float4* bnd16 = reinterpret_cast<float4*>(base + L.bnd16);
-  double* box = reinterpret_cast<double*>(base + L.box);
   uint64_t* keys = reinterpret_cast<uint64_t*>(base + L.keys);
   p->view.src = src;
   p->view.q = q;
@@ -919,30 +917,19 @@ int nfr_problem_create_periodic(nfr_context* ctx, int64_t n, const double* xyz_d
   p->view.bnd32 = bnd32;
   p->view.bnd16 = bnd16;
   hipStream_t st = ctx->stream;
-  hipLaunchKernelGGL(k_pack, dim3((unsigned)ceil_div(npad, kWG)), dim3(kWG), 0, st, xyz_dev, q_dev, n, npad, period, src, q,
-                     xyz);
-  hipLaunchKernelGGL(k_qmax, dim3(1), dim3(kWG), 0, st, q, src, npad, qmax);
-  // tile order (kernels_tile.h): recursive bisection, each level a bitonic sort
-  // of (segment, coordinate along the segment's longest axis, node) keys;
-  // then the slot arrays and block bounds
-  const int64_t np2 = tile_pow2(npad);
-  const dim3 gk((unsigned)ceil_div(np2, kWG));
-  hipLaunchKernelGGL(k_tile_init, dim3((unsigned)ceil_div(n, kWG)), dim3(kWG), 0, st, n, perm);
-  const int levels = tile_levels(n);
-  for (int l = 0; l < levels; ++l) {
-    hipLaunchKernelGGL(k_tile_seg_box, dim3((unsigned)(int64_t(1) << l)), dim3(kWG), 0, st, src, perm, n, l, box);
-    hipLaunchKernelGGL(k_tile_seg_keys, gk, dim3(kWG), 0, st, src, perm, n, np2, l, box, keys);
-    for (int64_t k = 2; k <= np2; k <<= 1)
-      for (int64_t j = k >> 1; j > 0; j >>= 1) hipLaunchKernelGGL(k_bitonic, gk, dim3(kWG), 0, st, keys, np2, k, j);
-    hipLaunchKernelGGL(k_tile_take, dim3((unsigned)ceil_div(n, kWG)), dim3(kWG), 0, st, keys, n, perm);
-  }
-  hipLaunchKernelGGL(k_tile_build, dim3((unsigned)ceil_div(npad, kWG)), dim3(kWG), 0, st, n, npad, src, q, perm, src_t,
-                     q_t);
+  const unsigned nblk = (unsigned)ceil_div(npad, kWG);
+  double* blockmax = reinterpret_cast<double*>(keys);   // 2 per workgroup, before the keys
+  hipLaunchKernelGGL(k_pack, dim3(nblk), dim3(kWG), 0, st, xyz_dev, q_dev, n, npad, period, src, q, xyz, blockmax);
+  hipLaunchKernelGGL(k_qmax, dim3(1), dim3(kWG), 0, st, blockmax, (int64_t)nblk, qmax);
+  // tile order (kernels_tile.h), then the slot arrays and block bounds
+  const int levels = tile_levels(n), split = std::min(levels, tile_split_levels(n));
+  for (int l = 0; l < split; ++l)
+    hipLaunchKernelGGL(k_tile_split, dim3((unsigned)(int64_t(1) << l)), dim3(kTileThreads), 0, st, src, n, l, l == 0 ? 1 : 0, keys, perm);
+  hipLaunchKernelGGL(k_tile_local, dim3((unsigned)(int64_t(1) << split)), dim3(kTileLocal), 0, st, src, n, split, levels,
+                     split == 0 ? 1 : 0, perm);
+  hipLaunchKernelGGL(k_tile_build, dim3(nblk), dim3(kWG), 0, st, n, npad, src, q, perm, src_t, q_t);
   const int64_t nb32 = npad / kTileRowBlock, nb16 = npad / kTileColBlock;
-  hipLaunchKernelGGL(k_tile_bounds<kTileRowBlock>, dim3((unsigned)ceil_div(nb32, kWG)), dim3(kWG), 0, st, src_t, n, nb32,
-                     bnd32);
-  hipLaunchKernelGGL(k_tile_bounds<kTileColBlock>, dim3((unsigned)ceil_div(nb16, kWG)), dim3(kWG), 0, st, src_t, n, nb16,
-                     bnd16);
+  hipLaunchKernelGGL(k_tile_bounds, dim3((unsigned)ceil_div(nb32 + nb16, 64)), dim3(64), 0, st, src_t, n, nb32, nb16, bnd32, bnd16);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     delete p;
