@@ -355,7 +355,8 @@ __global__ __launch_bounds__(kWG) void k_quad_proj(const double* __restrict__ xy
 // with rho = d sec(alpha) and l = d tan(alpha) (l measured along p -> q from
 // the foot of the perpendicular) the antiderivative times d^4 reads
 //   rho^3 l / 4 + 3 d^2 rho l / 8 + 3 d^4 log(rho + l) / 8.
-// log(rho + l) for l < 0 is taken as 2 log d - log(rho - l) (no cancellation).
+// For l < 0, rho + l = d^2 / (rho - l) (no cancellation); the difference of the
+// two logarithms is taken as the logarithm of one quotient.
 __device__ inline double r3_apex(double Px, double Py, double px, double py, double qx, double qy) {
   const double ex = qx - px, ey = qy - py;
   const double len = sqrt(ex * ex + ey * ey);
@@ -369,9 +370,11 @@ __device__ inline double r3_apex(double Px, double Py, double px, double py, dou
   const double rq = sqrt(d2 + lq * lq);
   double val = 0.25 * (rq * rq * rq * lq - rp * rp * rp * lp) + 0.375 * d2 * (rq * lq - rp * lp);
   if (d > 0.0) {
-    const double Lq = lq >= 0.0 ? log(rq + lq) : 2.0 * log(d) - log(rq - lq);
-    const double Lp = lp >= 0.0 ? log(rp + lp) : 2.0 * log(d) - log(rp - lp);
-    val += 0.375 * d2 * d2 * (Lq - Lp);
+    const double num = lp >= 0.0 ? rq + lq : rp - lp;
+    const double den = lp >= 0.0 ? rp + lp : rq - lq;
+    // lp < 0 <= lq: the two sides of the foot, log(rq + lq) + log(rp - lp) - 2 log d
+    const double L = (lp < 0.0 && lq >= 0.0) ? log((rq + lq) / d) + log(num / d) : log(num / den);
+    val += 0.375 * d2 * d2 * L;
   }
   return d * val / 5.0;
 }
@@ -407,20 +410,53 @@ __device__ inline double mono2(int m, double x, double y) {
 
 constexpr int kQuadMaxK = 57;   // k + 7 <= 64: one lane per column of the system and its right-hand side
 
-// One wave per triangle t: pull-back, Jacobian, planar system in LDS
-// ((k+6) rows of k+7 FP64: matrix and right-hand side), LU with partial
-// pivoting (largest magnitude, first row on ties), back substitution;
-// wE[t*k + r] = w_r h_t^2 J_r.  Dynamic LDS: (k+6)(k+7) doubles + 2k doubles.
+__device__ __forceinline__ double readlane_f64(double v, int lane) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// Maximum over the 64 lanes of a wave (DPP moves fused into the maximum; lane 63 holds it).
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  auto step = [&](auto ctrl, auto rows) {
+    const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, decltype(rows)::value, 0xF, false);
+    v = v > o ? v : o;
+  };
+  using std::integral_constant;
+  step(integral_constant<int, 0xB1>{}, integral_constant<int, 0xF>{});    // quad_perm [1, 0, 3, 2]
+  step(integral_constant<int, 0x4E>{}, integral_constant<int, 0xF>{});    // quad_perm [2, 3, 0, 1]
+  step(integral_constant<int, 0x141>{}, integral_constant<int, 0xF>{});   // row_half_mirror
+  step(integral_constant<int, 0x140>{}, integral_constant<int, 0xF>{});   // row_mirror
+  step(integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});   // row_bcast15 into rows 1 and 3
+  step(integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});   // row_bcast31 into rows 2 and 3
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// One wave per triangle t: pull-back, Jacobian, planar system, LU with partial
+// pivoting, back substitution; wE[t*k + r] = w_r h_t^2 J_r.
+//
+// Lane r holds row r of the (k+6) x (k+6) system and its right-hand side in
+// registers, with the kernel columns at 0 .. k-1 and the polynomial columns at
+// KP .. KP+5 (KP >= k, the size the registers are cut for; the columns between
+// are skipped).  Rows are not moved: a step takes the pivot among the lanes
+// still available, and every other available lane subtracts its multiple of
+// the pivot lane's row, whose elements reach the wave as scalars (two lane
+// reads per multiply-add).  Pivots are compared by the upper 32 bits of their
+// magnitude (20 of 52 mantissa bits), the lowest lane among equals.  Bound by
+// instruction issue: about 750 multiply-adds, 1500 lane reads and 32 square
+// roots per lane at k = 32 (2, 3 or 4 waves per SIMD: the same time).
+// N = 65538, k = 32 (131072 triangles): 2.02 ms; 4.73 ms with the matrix in LDS
+// and a lane per column (barriers and LDS latency in every step).
+template <int KP>
 __global__ __launch_bounds__(64) void k_quad_elements(const double* __restrict__ xyz, const double* __restrict__ nrm,
                                                       const int* __restrict__ tri, const double* __restrict__ cen,
                                                       const double* __restrict__ nrm_tri,
                                                       const double* __restrict__ proj, const int* __restrict__ st,
                                                       int64_t n, int64_t ntri, int k, double* __restrict__ wE) {
-  extern __shared__ double lds[];
+  constexpr int D = KP + 6;
+  __shared__ double s_poly[6][KP];     // polynomial rows (the transposed polynomial columns)
   const int dim = k + 6;
-  const int ld = k + 7;
-  double* M = lds;                 // dim x ld
-  double* s2 = lds + dim * ld;     // k x 2 planar stencil coordinates
   const int64_t t = blockIdx.x;
   const int lane = threadIdx.x;
   if (t >= ntri) return;
@@ -505,28 +541,33 @@ __global__ __launch_bounds__(64) void k_quad_elements(const double* __restrict__
     }
   }
   const double sx = rel1 / h, sy = rel2 / h;
-  if (lane < k) {
-    s2[2 * lane] = sx;
-    s2[2 * lane + 1] = sy;
+
+  // rows r < k: [|s_r - s_c|^3 (c < k) | pi_m(s_r) | int_E |s - s_r|^3]
+  // rows k + m: [pi_m(s_c) (c < k) | 0 | int_E pi_m]
+  double a[D], rhs = 0.0;
+#pragma unroll
+  for (int c = 0; c < KP; ++c) {
+    a[c] = 0.0;
+    if (c < k) {
+      const double dx = sx - readlane_f64(sx, c), dy = sy - readlane_f64(sy, c);
+      const double r2 = dx * dx + dy * dy;
+      a[c] = r2 * sqrt(r2);
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < 6; ++m) {
+    a[KP + m] = mono2(m, sx, sy);
+    if (lane < k) s_poly[m][lane] = a[KP + m];
   }
   __syncthreads();
-
-  // assemble: rows r < k: [|s_r - s_c|^3 (c < k) | pi_m(s_r) | int_E |s - s_r|^3]
-  //           rows k + m: [pi_m(s_c) (c < k) | 0 | int_E pi_m]
   if (lane < k) {
-    double* row = M + lane * ld;
-    for (int c = 0; c < k; ++c) {
-      const double dx = sx - s2[2 * c], dy = sy - s2[2 * c + 1];
-      const double r = sqrt(dx * dx + dy * dy);
-      row[c] = r * r * r;
-    }
-    for (int m = 0; m < 6; ++m) row[k + m] = mono2(m, sx, sy);
-    row[dim] = r3_triangle(sx, sy, v);
+    rhs = r3_triangle(sx, sy, v);
   } else if (lane < dim) {
     const int m = lane - k;
-    double* row = M + lane * ld;
-    for (int c = 0; c < k; ++c) row[c] = mono2(m, s2[2 * c], s2[2 * c + 1]);
-    for (int c = k; c < dim; ++c) row[c] = 0.0;
+#pragma unroll
+    for (int c = 0; c < KP; ++c) a[c] = c < k ? s_poly[m][c] : 0.0;
+#pragma unroll
+    for (int c = KP; c < D; ++c) a[c] = 0.0;
     // exact for degree 2: area / 3 times the sum over the edge midpoints
     const double area = 0.5 * fabs(cross2(v[1][0] - v[0][0], v[1][1] - v[0][1], v[2][0] - v[0][0], v[2][1] - v[0][1]));
     double acc = 0.0;
@@ -534,46 +575,42 @@ __global__ __launch_bounds__(64) void k_quad_elements(const double* __restrict__
       const int f = (e + 1) % 3;
       acc += mono2(m, 0.5 * (v[e][0] + v[f][0]), 0.5 * (v[e][1] + v[f][1]));
     }
-    row[dim] = acc * (area / 3.0);
+    rhs = acc * (area / 3.0);
   }
-  __syncthreads();
 
-  // LU with partial pivoting; lane c owns column c of the trailing update
-  for (int col = 0; col < dim; ++col) {
-    double best = (lane >= col && lane < dim) ? fabs(M[lane * ld + col]) : -1.0;
-    int bi = lane;
-    for (int off = 32; off > 0; off >>= 1) {
-      const double ob = __shfl_xor(best, off);
-      const int oi = __shfl_xor(bi, off);
-      if (ob > best || (ob == best && oi < bi)) {
-        best = ob;
-        bi = oi;
-      }
-    }
-    if (bi != col && lane <= dim) {
-      const double a = M[col * ld + lane];
-      M[col * ld + lane] = M[bi * ld + lane];
-      M[bi * ld + lane] = a;
-    }
-    __syncthreads();
-    const double pv = M[col * ld + col];
-    if (lane > col && lane < dim) M[lane * ld + col] /= pv;
-    __syncthreads();
-    if (lane > col && lane <= dim) {
-      const double top = M[col * ld + lane];
-      for (int r = col + 1; r < dim; ++r) M[r * ld + lane] -= M[r * ld + col] * top;
-    }
-    __syncthreads();
+  uint64_t avail = dim < 64 ? (1ull << dim) - 1 : ~0ull;   // rows that have not been pivots
+  int row_of = 0;                                           // lane c: the pivot row of column c
+  double diag = 1.0;                                        // this row's pivot
+#pragma unroll
+  for (int col = 0; col < D; ++col) {
+    if (col < KP && col >= k) continue;
+    const bool mine = (avail >> lane) & 1;
+    const uint32_t mag = mine ? (uint32_t)(__builtin_bit_cast(uint64_t, a[col]) >> 32) & 0x7fffffffu : 0u;
+    const uint32_t top = wave_max_u32(mag);
+    const int p = __builtin_ctzll(__ballot(mine && mag == top));
+    avail &= ~(1ull << p);
+    row_of = lane == col ? p : row_of;
+    const double pv = readlane_f64(a[col], p);
+    diag = lane == p ? pv : diag;
+    const double l = (mine && lane != p) ? a[col] / pv : 0.0;
+#pragma unroll
+    for (int c = col + 1; c < D; ++c) a[c] = fma(-l, readlane_f64(a[c], p), a[c]);
+    rhs = fma(-l, readlane_f64(rhs, p), rhs);
   }
-  // back substitution on the right-hand-side column
-  for (int r = dim - 1; r >= 0; --r) {
-    const double xr = M[r * ld + dim] / M[r * ld + r];
-    __syncthreads();
-    if (lane < r) M[lane * ld + dim] -= M[lane * ld + r] * xr;
-    if (lane == r) M[r * ld + dim] = xr;
-    __syncthreads();
+  // back substitution: every lane subtracts, only rows still to be solved matter
+  const double rdiag = 1.0 / diag;
+  double w = 0.0;
+#pragma unroll
+  for (int col = D - 1; col >= 0; --col) {
+    if (col < KP && col >= k) continue;
+    const int p = __builtin_amdgcn_readlane(row_of, col);
+    double x = rhs * rdiag;
+    x = fma(fma(-diag, x, rhs), rdiag, x);
+    const double xc = readlane_f64(x, p);
+    rhs = fma(-a[col], xc, rhs);
+    w = lane == col ? xc : w;
   }
-  if (lane < k) wE[t * k + lane] = M[lane * ld + dim] * h * h * J;
+  if (lane < k) wE[t * k + lane] = w * h * h * J;
 }
 
 // ------------------------------------------------------------------ accumulation

@@ -2115,9 +2115,15 @@ int nfr_quad_weights(nfr_context* ctx, int64_t n, const double* xyz_dev, const d
   hipLaunchKernelGGL(k_quad_bin_fill, dim3(nbn), dim3(kWG), 0, s, xyz_dev, n, w.grid, w.gstart, w.gcursor, w.gnodes);
   hipLaunchKernelGGL(k_quad_knn, dim3((unsigned)ceil_div(ntri, kWG / 64)), dim3(kWG), 0, s, xyz_dev, w.grid, w.gcnt,
                      w.gstart, w.gnodes, w.cen, ntri, k, stn);
-  const size_t lds = (size_t(k + 6) * (k + 7) + 2 * size_t(k)) * sizeof(double);
-  hipLaunchKernelGGL(k_quad_elements, dim3((unsigned)ntri), dim3(64), lds, s, xyz_dev, nrm_dev, w.tri, w.cen,
-                     w.nrm_tri, proj, stn, n, ntri, k, w.wE);
+  // registers for the smallest of four sizes that holds k (32 is the default stencil)
+#define NFR_QUAD_ELEMENTS(KP)                                                                                     \
+  hipLaunchKernelGGL(k_quad_elements<KP>, dim3((unsigned)ntri), dim3(64), 0, s, xyz_dev, nrm_dev, w.tri, w.cen, \
+                     w.nrm_tri, proj, stn, n, ntri, k, w.wE)
+  if (k <= 20) NFR_QUAD_ELEMENTS(20);
+  else if (k <= 32) NFR_QUAD_ELEMENTS(32);
+  else if (k <= 45) NFR_QUAD_ELEMENTS(45);
+  else NFR_QUAD_ELEMENTS(57);
+#undef NFR_QUAD_ELEMENTS
   const unsigned eb = (unsigned)ceil_div((int64_t)tk, kWG);
   const int64_t nb = ceil_div(n, kWG);
   hipLaunchKernelGGL(k_quad_count, dim3(eb), dim3(kWG), 0, s, stn, (int64_t)tk, n, w.cnt);
