@@ -688,10 +688,13 @@ int check_w(const nfr_problem* p, int form, const void* w_dev) {
 namespace {
 // Regions of a problem's pack buffer, in order: packed coordinates, weights,
 // FP64 coordinates, the two maxima, then the tile order (kernels_tile.h):
-// slot -> node, coordinates and weights in slot order, block bounds, and the
-// scratch of the problem's creation (block maxima, then selection keys).
+// slot -> node, coordinates and weights in slot order, block bounds, 48 bytes
+// per segment of the deepest bisection level, and 64-bit words for the next
+// power of two of the nodes, scratch of the problem's creation (block maxima,
+// then selection keys).  The sizes are part of the boundary: callers hold
+// buffers of nfr_problem_bytes.
 struct PackLayout {
-  size_t src, q, xyz, qmax, perm, src_t, q_t, bnd32, bnd16, keys, bytes;
+  size_t src, q, xyz, qmax, perm, src_t, q_t, bnd32, bnd16, seg, keys, bytes;
 };
 PackLayout pack_layout(int64_t n) {
   const int64_t npad = round_up(n, kPad);
@@ -711,7 +714,10 @@ PackLayout pack_layout(int64_t n) {
   L.q_t = take(npad * sizeof(double));
   L.bnd32 = take(npad / kTileRowBlock * sizeof(float4));
   L.bnd16 = take(npad / kTileColBlock * sizeof(float4));
-  L.keys = take(npad * sizeof(uint64_t));
+  L.seg = take(size_t(48) << tile_levels(n));
+  int64_t np2 = 1;
+  while (np2 < npad) np2 *= 2;
+  L.keys = take(np2 * sizeof(uint64_t));
   L.bytes = off;
   return L;
 }
