@@ -767,35 +767,85 @@ struct KernelF64 {
   double period;   // > 0: periodic problem (x, y reduced to one period window)
 };
 
-// Squared distance in FP64, with the per-axis nearest image of a periodic problem.
-__device__ inline double pair_r2_64(const KernelF64& k, double dx, double dy, double dz) {
-  if (k.period > 0.0) {
+// 2^y in FP64 for y <= 0, y below -1000 (and NaN) as 2^-1000, which is 0 in
+// every type W is stored in: n = rint(y), f = y - n, 2^f = 1 + f P(f) with P the
+// degree-10 interpolant of (2^f - 1) / f at the Chebyshev nodes of [-1/2, 1/2]
+// (relative error 2e-17), n added to the exponent.
+__device__ __forceinline__ double exp2_64(double y) {
+  y = fmax(y, -1000.0);
+  const double n = rint(y);
+  const double f = y - n;
+  double p = 0x1.e9d3fe3952179p-32;
+  p = fma(p, f, 0x1.e6063f7217bc6p-28);
+  p = fma(p, f, 0x1.b524fae627834p-24);
+  p = fma(p, f, 0x1.62bfd47773353p-20);
+  p = fma(p, f, 0x1.ffcbfc670dcd4p-17);
+  p = fma(p, f, 0x1.430913096fd9fp-13);
+  p = fma(p, f, 0x1.5d87fe78a5276p-10);
+  p = fma(p, f, 0x1.3b2ab6fba1ddap-7);
+  p = fma(p, f, 0x1.c6b08d704a0c2p-5);
+  p = fma(p, f, 0x1.ebfbdff82c598p-3);
+  p = fma(p, f, 0x1.62e42fefa39efp-1);
+  p = fma(p, f, 1.0);
+  return __builtin_bit_cast(double, __builtin_bit_cast(int64_t, p) + ((int64_t)(int)n << 52));
+}
+
+// w = A_e 2^-(c_e d) - A_i 2^-(c_i d) with d = r^2 (Gaussian) or r and
+// c = log2 e / s^2 or / s.
+struct WeightEval {
+  double ce, ci;
+};
+
+__host__ inline WeightEval weight_eval(const KernelF64& k) {
+  WeightEval w;
+  w.ce = kLog2e / (k.kind == 0 ? k.se * k.se : k.se);
+  w.ci = kLog2e / (k.kind == 0 ? k.si * k.si : k.si);
+  return w;
+}
+
+// KIND: kernel kind, + 2 for a periodic problem.  Ae: the amplitude A_e, NaN
+// for a row with a coordinate that is not finite (row_amp); a column with a NaN
+// carries it in its weight (the exponentials drop NaN arguments).
+template <int KIND>
+__device__ __forceinline__ double kernel_w64(const KernelF64& k, const WeightEval& w, double Ae, double dx, double dy,
+                                             double dz) {
+  if (KIND & 2) {
     dx = fabs(dx);
     dx = fmin(dx, k.period - dx);
     dy = fabs(dy);
     dy = fmin(dy, k.period - dy);
   }
-  return dx * dx + dy * dy + dz * dz;
+  const double r2 = dx * dx + dy * dy + dz * dz;
+  const double d = (KIND & 1) ? sqrt(r2) : r2;
+  return Ae * exp2_64(-(d * w.ce)) - k.Ai * exp2_64(-(d * w.ci));
 }
 
-__device__ inline double kernel_w64(const KernelF64& k, double r2) {
-  if (k.kind == 0) return k.Ae * exp(-r2 / (k.se * k.se)) - k.Ai * exp(-r2 / (k.si * k.si));
-  const double r = sqrt(r2);
-  return k.Ae * exp(-r / k.se) - k.Ai * exp(-r / k.si);
+__device__ __forceinline__ double row_amp(double Ae, double x, double y, double z) {
+  return Ae + ((x - x) + (y - y) + (z - z));
+}
+
+__device__ __forceinline__ double col_weight(double q, double x, double y, double z) {
+  return x != x || y != y || z != z ? x + y + z : q;
 }
 
 // W[i*npad + j] = w(|x_i - x_j|) q_j, FP64 arithmetic rounded once to FP32;
 // rows i < n, columns j < npad (zero where q_j = 0).
-// Grid: x = rows, y = column blocks of kWG.
+// Grid: x = blocks of kWBuildRows rows, y = column blocks of kWG.  A thread
+// keeps its column and walks the rows, whose coordinates are uniform.
+constexpr int kWBuildRows = 32;
+template <int KIND>
 __global__ __launch_bounds__(kWG) void k_w_build_f32(const double* __restrict__ xyz64, const double* __restrict__ qd,
-                                                     int64_t n, int64_t npad, KernelF64 kp, float* __restrict__ W) {
-  const int64_t i = blockIdx.x;
-  const int64_t j = (int64_t)blockIdx.y * kWG + threadIdx.x;
-  if (i >= n || j >= npad) return;
-  const double r2 = pair_r2_64(kp, xyz64[3 * i] - xyz64[3 * j], xyz64[3 * i + 1] - xyz64[3 * j + 1],
-                               xyz64[3 * i + 2] - xyz64[3 * j + 2]);
-  const double wq = qd[j] == 0.0 ? 0.0 : kernel_w64(kp, r2) * qd[j];
-  W[i * npad + j] = (float)wq;
+                                                     int64_t n, int64_t npad, KernelF64 kp, WeightEval we,
+                                                     float* __restrict__ W) {
+  const int64_t i0 = (int64_t)blockIdx.x * kWBuildRows;
+  const int64_t j = (int64_t)blockIdx.y * kWG + threadIdx.x;   // npad is a multiple of kWG
+  const double xj = xyz64[3 * j], yj = xyz64[3 * j + 1], zj = xyz64[3 * j + 2];
+  const double qj = qd[j] == 0.0 ? 0.0 : col_weight(qd[j], xj, yj, zj);
+  const int64_t i1 = i0 + kWBuildRows < n ? i0 + kWBuildRows : n;
+  for (int64_t i = i0; i < i1; ++i) {
+    const double xi = xyz64[3 * i], yi = xyz64[3 * i + 1], zi = xyz64[3 * i + 2];
+    W[i * npad + j] = (float)(kernel_w64<KIND>(kp, we, row_amp(kp.Ae, xi, yi, zi), xi - xj, yi - yj, zi - zj) * qj);
+  }
 }
 
 // Row-blocked GEMV / small GEMM with W streamed from HBM:

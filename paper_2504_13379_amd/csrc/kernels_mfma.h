@@ -99,64 +99,73 @@ __device__ inline void split_hi_lo(double x, T& hi, T& lo) {
   lo = to_half_type<T>(r * (double)(1 << MfmaTraits<T>::c));
 }
 
-// One workgroup: header[0] = sW, header[1] = 2^-sW, header[2] = 2^-(sW + c).
-// FP16: sW = 14 - ceil(log2((|A_e| + |A_i|) max_j |q_j|)) puts the largest
-// possible |W| just below 2^14.  BF16: sW = 0.
+// header[0] = sW, header[1] = 2^-sW, header[2] = 2^-(sW + c).  FP16: sW =
+// 14 - ceil(log2((|A_e| + |A_i|) max_j |q_j|)) puts the largest possible |W|
+// just below 2^14.  BF16: sW = 0.
 template <typename T>
-__global__ __launch_bounds__(kWG) void k_mfma_scale(const double* __restrict__ qd, int64_t npad, double amp,
-                                                    int is_fp16, float* __restrict__ header) {
-  __shared__ double red[kWG];
-  double m = 0.0;
-  for (int64_t j = threadIdx.x; j < npad; j += kWG) m = fmax(m, fabs(qd[j]));
-  red[threadIdx.x] = m;
-  __syncthreads();
-  for (int s = kWG / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + s]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    int sW = 0;
-    const double bound = amp * red[0];
-    if (is_fp16 && bound > 0.0) sW = 14 - (int)ceil(log2(bound));
+__device__ inline int w_scale_exp(const double* __restrict__ qmax, double amp) {
+  const double bound = amp * qmax[0];
+  return MfmaTraits<T>::fp16 && bound > 0.0 ? 14 - (int)ceil(log2(bound)) : 0;
+}
+
+// Whi/Wlo in fragment order; zero for rows i >= n or q_j = 0.
+//
+// Bound by FP64 vector issue (a distance, two exponentials and the split per
+// entry) and by writing the matrix.  A wave owns one 16-column block and walks
+// kWBuildGroups groups of four row blocks: lane m + 32 h keeps its 8 columns'
+// coordinates and weights in registers, loads one row per row block and
+// stores its 8 entries as one 16-byte chunk per matrix, so a wave writes 8 KB
+// of consecutive memory per group.  (With one row per workgroup every thread
+// loaded 32 strided doubles for its 8 entries, and the exponentials took the
+// library's general path after an FP64 division: 7.35 ms at N = 32768, now
+// 2.6, of which writing takes about 0.8.)
+// Grid: x = row groups / kWBuildGroups, y = 16-column blocks / 4.
+constexpr int kWBuildGroups = 4;
+template <typename T, int KIND>
+__global__ __launch_bounds__(kWG) void k_mfma_w_build(const double* __restrict__ xyz64, const double* __restrict__ qd,
+                                                      int64_t n, int64_t npad, KernelF64 kp, WeightEval we,
+                                                      const double* __restrict__ qmax, double amp,
+                                                      float* __restrict__ header, T* __restrict__ Wt) {
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, m = lane & 31, h = lane >> 5;
+  const int64_t kb = (int64_t)blockIdx.y * 4 + (tid >> 6);     // npad / 16 is a multiple of 4
+  const int sW = w_scale_exp<T>(qmax, amp);
+  if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) {
     header[0] = (float)sW;
     header[1] = (float)ldexp(1.0, -sW);
     header[2] = (float)ldexp(1.0, -(sW + MfmaTraits<T>::c));
     header[3] = 0.0f;
   }
-}
-
-// Whi/Wlo in fragment order; zero for rows i >= n or q_j = 0.  A thread
-// builds the 8 entries W_i,8g .. W_i,8g+7 (one lane's share of one tile) and
-// stores them as one 16-byte chunk per matrix.
-// Grid: x = rows (npad), y = blocks of kWG column groups (npad / 8 groups).
-template <typename T>
-__global__ __launch_bounds__(kWG) void k_mfma_w_build(const double* __restrict__ xyz64, const double* __restrict__ qd,
-                                                      int64_t n, int64_t npad, KernelF64 kp,
-                                                      const float* __restrict__ header, T* __restrict__ Wt) {
-  const int64_t i = blockIdx.x;
-  const int64_t g = (int64_t)blockIdx.y * kWG + threadIdx.x;
-  if (i >= npad || g >= npad / 8) return;
-  const double scale = ldexp(1.0, (int)header[0]);
-  T hi[8], lo[8];
+  const double scale = ldexp(1.0, sW);
+  double x[8], y[8], z[8], q[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    const int64_t j = 8 * g + e;
-    double wq = 0.0;
-    if (i < n && qd[j] != 0.0) {
-      const double r2 = pair_r2_64(kp, xyz64[3 * i] - xyz64[3 * j], xyz64[3 * i + 1] - xyz64[3 * j + 1],
-                                   xyz64[3 * i + 2] - xyz64[3 * j + 2]);
-      wq = kernel_w64(kp, r2) * qd[j] * scale;
-    }
-    split_hi_lo<T>(wq, hi[e], lo[e]);
+    const int64_t j = 16 * kb + 8 * h + e;
+    x[e] = xyz64[3 * j];
+    y[e] = xyz64[3 * j + 1];
+    z[e] = xyz64[3 * j + 2];
+    q[e] = qd[j] == 0.0 ? 0.0 : col_weight(qd[j], x[e], y[e], z[e]) * scale;
   }
-  const int64_t rb = i >> 5, m = i & 31, kb = g >> 1, h = g & 1;
-  const int64_t tile_hi = (((rb >> 2) * (npad / 16) + kb) * 2) * 4 + (rb & 3);
-  const int64_t off = tile_hi * 512 + (m + 32 * h) * 8;
-  u32x4_t vh, vl;
-  __builtin_memcpy(&vh, hi, 16);
-  __builtin_memcpy(&vl, lo, 16);
-  *reinterpret_cast<u32x4_t*>(Wt + off) = vh;
-  *reinterpret_cast<u32x4_t*>(Wt + off + 4 * 512) = vl;
+  const int64_t ngroups = npad / kMfmaRowsPerWG;
+  for (int64_t g = (int64_t)blockIdx.x * kWBuildGroups; g < ngroups && g < ((int64_t)blockIdx.x + 1) * kWBuildGroups; ++g) {
+    T* const dst = Wt + ((g * (npad / 16) + kb) * 8) * 512 + lane * 8;
+#pragma unroll 1
+    for (int r = 0; r < 4; ++r) {
+      const int64_t i = g * kMfmaRowsPerWG + r * 32 + m;
+      const double xi = xyz64[3 * i], yi = xyz64[3 * i + 1], zi = xyz64[3 * i + 2];
+      const double Ae = row_amp(kp.Ae, xi, yi, zi);
+      T hi[8], lo[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        split_hi_lo<T>(kernel_w64<KIND>(kp, we, Ae, xi - x[e], yi - y[e], zi - z[e]) * q[e], hi[e], lo[e]);
+      u32x4_t vh, vl;
+      __builtin_memcpy(&vh, hi, 16);
+      __builtin_memcpy(&vl, lo, 16);
+      if (i >= n) vh = vl = u32x4_t{0u, 0u, 0u, 0u};
+      __builtin_nontemporal_store(vh, reinterpret_cast<u32x4_t*>(dst + r * 512));
+      __builtin_nontemporal_store(vl, reinterpret_cast<u32x4_t*>(dst + (4 + r) * 512));
+    }
+  }
 }
 
 // 14 - ceil(log2(bound)) for FP16 (puts |x| <= bound just below 2^14), else 0;
@@ -1215,10 +1224,17 @@ template <typename T>
 inline void launch_mfma_w_build_t(const ProblemView& pv, const KernelF64& kp, void* W, hipStream_t s) {
   MfmaBufs m = mfma_bufs(W, pv.npad);
   const double amp = fabs(kp.Ae) + fabs(kp.Ai);
-  hipLaunchKernelGGL(k_mfma_scale<T>, dim3(1), dim3(kWG), 0, s, pv.q, pv.npad, amp,
-                     (int)MfmaTraits<T>::fp16, const_cast<float*>(m.header));
-  hipLaunchKernelGGL(k_mfma_w_build<T>, dim3((unsigned)pv.npad, (unsigned)ceil_div(pv.npad / 8, kWG)), dim3(kWG), 0, s,
-                     pv.xyz, pv.q, pv.n, pv.npad, kp, m.header, static_cast<T*>(m.tiles));
+  const dim3 grid((unsigned)ceil_div(pv.npad / kMfmaRowsPerWG, kWBuildGroups), (unsigned)(pv.npad / 64));
+  auto launch = [&](auto kind) {
+    hipLaunchKernelGGL((k_mfma_w_build<T, decltype(kind)::value>), grid, dim3(kWG), 0, s, pv.xyz, pv.q, pv.n, pv.npad, kp,
+                       weight_eval(kp), pv.qmax, amp, const_cast<float*>(m.header), static_cast<T*>(m.tiles));
+  };
+  switch (kp.kind + (kp.period > 0.0 ? 2 : 0)) {
+    case 0: launch(std::integral_constant<int, 0>()); break;
+    case 1: launch(std::integral_constant<int, 1>()); break;
+    case 2: launch(std::integral_constant<int, 2>()); break;
+    default: launch(std::integral_constant<int, 3>()); break;
+  }
 }
 
 inline void launch_mfma_w_build(const ProblemView& pv, int form, const KernelF64& kp, void* W, hipStream_t s) {

@@ -1029,8 +1029,17 @@ int nfr_w_build(nfr_problem* prob, const nfr_kernel* kernel, int form, void* w_d
   NFR_HIP(hipSetDevice(prob->ctx->device));
   hipStream_t s = prob->ctx->stream;
   if (form == NFR_FORM_W_FP32) {
-    hipLaunchKernelGGL(k_w_build_f32, dim3((unsigned)pv.n, (unsigned)ceil_div(pv.npad, kWG)), dim3(kWG), 0, s, pv.xyz,
-                       pv.q, pv.n, pv.npad, kernel64(*kernel, pv), static_cast<float*>(w_dev));
+    const KernelF64 kp = kernel64(*kernel, pv);
+    auto launch = [&](auto kind) {
+      hipLaunchKernelGGL(k_w_build_f32<decltype(kind)::value>, dim3((unsigned)ceil_div(pv.n, kWBuildRows), (unsigned)(pv.npad / kWG)),
+                         dim3(kWG), 0, s, pv.xyz, pv.q, pv.n, pv.npad, kp, weight_eval(kp), static_cast<float*>(w_dev));
+    };
+    switch (kind_code(*kernel, pv)) {
+      case 0: launch(std::integral_constant<int, 0>()); break;
+      case 1: launch(std::integral_constant<int, 1>()); break;
+      case 2: launch(std::integral_constant<int, 2>()); break;
+      default: launch(std::integral_constant<int, 3>()); break;
+    }
   } else {
     launch_mfma_w_build(pv, form, kernel64(*kernel, pv), w_dev, s);
   }
