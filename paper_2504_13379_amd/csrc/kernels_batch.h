@@ -53,7 +53,8 @@ __host__ __device__ constexpr int batch_bs(int B) { return B == 1 ? 1 : (B <= 4 
 __host__ __device__ constexpr int batch_tpt(int bs) { return bs == 16 ? NFR_BATCH_TPT16 : otf_tpt(bs); }
 
 template <int KIND>
-__device__ inline void batch_item(const BatchProblemDev& P, const BatchItem& w, float4* s_src, float (*s_g)[kWG]) {
+__device__ inline void batch_item(const BatchProblemDev& P, const BatchItem& w, float4* s_src,
+                                  float (*s_g)[kOtfGStride]) {
   if (P.bs == 1)
     otf_tile<KIND, batch_tpt(1), 1>(P.src, P.g, P.npad, P.B, P.chunk, P.pp, P.part, w.tile, w.split, w.sb, s_src, s_g);
   else if (P.bs == 4)
@@ -67,7 +68,7 @@ __device__ inline void batch_item(const BatchProblemDev& P, const BatchItem& w, 
 __global__ __launch_bounds__(kWG) void k_batch_pairs(const BatchProblemDev* __restrict__ probs,
                                                      const BatchItem* __restrict__ items, int nitems) {
   __shared__ float4 s_src[kWG];
-  __shared__ float s_g[16][kWG];
+  __shared__ float s_g[16][kOtfGStride];
   for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
     const BatchItem w = items[it];
     const BatchProblemDev& P = probs[w.p];

@@ -156,10 +156,12 @@ __device__ __forceinline__ float pair_u(float t, float rho, float kappa) {
 // Targets per thread for a block of BS states (TPT x BS accumulators per thread).
 __host__ __device__ constexpr int otf_tpt(int bs) { return bs <= 4 ? 4 : 2; }
 
+constexpr int kOtfGStride = kWG + 4;     // floats per LDS row of g: the matrix-core form reads 16 rows at once
+
 template <int KIND, int TPT, int BS>
 __device__ inline void otf_tile(const float4* __restrict__ src, const float* __restrict__ g, int64_t npad, int B,
                                 int64_t chunk, const PairParams& pp, double* __restrict__ part, int64_t tile,
-                                int split, int b0, float4* s_src, float (*s_g)[kWG]) {
+                                int split, int b0, float4* s_src, float (*s_g)[kOtfGStride]) {
   const int tid = threadIdx.x;
   const int64_t tbase = tile * (kWG * TPT);
 
@@ -232,12 +234,108 @@ __device__ inline void otf_tile(const float4* __restrict__ src, const float* __r
   }
 }
 
+// The same sums for blocks of BS = 16 NB states with the products on the FP32
+// matrix cores, one 16x16x1 MFMA (four blocks) per source and 16 states: a lane
+// evaluates the kernel for its target (the A operand: targets 16 b + m of the
+// wave in lane 16 b + m) and holds g of one state (the B operand).  Its one
+// product per entry rounds as the vector units' fused multiply-add, so every
+// sum is the same bit for bit, in the same order.  A kernel value serves all
+// states of the block; 64 pairs cost the matrix cores 32 clocks per 16 states,
+// where 16 vector multiply-adds take about 48, and the g values reach a wave
+// by one LDS read per four sources and 16 states instead of 16 broadcasts per
+// source.  Bound by vector issue and the FP32 matrix cores taking turns (about 43
+// clocks to evaluate 64 pairs, 32 per 16 states).  Per application with 16 / 32 /
+// 64 states: N = 20011 375 / 719 / 1488 -> 282 / 392 / 684 us, N = 65536 with 64
+// states 12.4 -> 5.9 ms; at 7 states the 8-state vector form takes 224 us, so the
+// matrix cores start at 9.
+// Output element r of lane l: target 16 (r / 4) + 4 (l / 16) + r % 4 of the
+// wave, state l % 16.
+typedef float f32x16v __attribute__((ext_vector_type(16)));
+
+template <int KIND, int NB>
+__device__ inline void otf_mfma_tile(const float4* __restrict__ src, const float* __restrict__ g, int64_t npad, int B,
+                                     int64_t chunk, const PairParams& pp, double* __restrict__ part, int64_t tile,
+                                     int split, int b0, float4* s_src, float (*s_g)[kOtfGStride]) {
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, m = lane & 15;
+  const int64_t t0 = tile * kWG + (tid - lane);   // the wave's targets (npad is a multiple of kWG)
+  const float4 p = src[t0 + lane];
+  const float xi = p.x * pp.sig, yi = p.y * pp.sig, zi = p.z * pp.sig;
+  double acc[NB][16];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[nb][r] = 0.0;
+
+  const int64_t j_begin = (int64_t)split * chunk;
+  int64_t j_end = j_begin + chunk;
+  if (j_end > npad) j_end = npad;
+  const float rho = pp.rho;
+  const float kappa = pp.kappa;
+  const int nv = B - b0 < 16 * NB ? B - b0 : 16 * NB;
+  for (int b = nv; b < 16 * NB; ++b) s_g[b][tid] = 0.0f;   // states beyond B
+
+  for (int64_t j0 = j_begin; j0 < j_end; j0 += kWG) {
+    {
+      const float4 s = src[j0 + tid];
+      s_src[tid] = make_float4(s.x * pp.sig, s.y * pp.sig, s.z * pp.sig, 0.0f);
+      const float* gp = g + (int64_t)b0 * npad + j0 + tid;
+#pragma unroll 8
+      for (int b = 0; b < nv; ++b, gp += npad) s_g[b][tid] = *gp;
+    }
+    __syncthreads();
+    f32x16v a[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) a[nb][r] = 0.0f;
+#pragma unroll 2
+    for (int jj = 0; jj < kWG; jj += 4) {
+      f32x4 gv[NB];
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) gv[nb] = *reinterpret_cast<const f32x4*>(&s_g[16 * nb + m][jj]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float4 s = s_src[jj + e];
+        const float r2 = pair_r2<KIND>(xi - s.x, yi - s.y, zi - s.z, pp.per);
+        const float t = ((KIND & 1) == 0) ? r2 : __builtin_amdgcn_sqrtf(r2);
+        const float u = pair_u<KIND>(t, rho, kappa);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) a[nb] = __builtin_amdgcn_mfma_f32_16x16x1f32(u, gv[nb][e], a[nb], 0, 0, 0);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[nb][r] += pp.amp * (double)a[nb][r];
+  }
+
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    const int b = b0 + 16 * nb + m;
+    if (b >= B) continue;
+    double* dst = part + ((int64_t)split * B + b) * npad + t0 + 4 * (lane >> 4);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dst[16 * (r / 4) + r % 4] = acc[nb][r];
+  }
+}
+
+template <int KIND, int NB>
+__global__ __launch_bounds__(kWG, 2) void k_otf_mfma_sum(const float4* __restrict__ src, const float* __restrict__ g,
+                                                         int64_t npad, int B, int64_t chunk, PairParams pp,
+                                                         double* __restrict__ part) {
+  __shared__ float4 s_src[kWG];
+  __shared__ __attribute__((aligned(16))) float s_g[16 * NB][kOtfGStride];
+  otf_mfma_tile<KIND, NB>(src, g, npad, B, chunk, pp, part, blockIdx.x, blockIdx.y, blockIdx.z * 16 * NB, s_src, s_g);
+}
+
 template <int KIND, int TPT, int BS>
 __global__ __launch_bounds__(kWG) void k_otf_pair_sum(const float4* __restrict__ src, const float* __restrict__ g,
                                                       int64_t npad, int B, int64_t chunk, PairParams pp,
                                                       double* __restrict__ part) {
   __shared__ float4 s_src[kWG];
-  __shared__ float s_g[BS][kWG];
+  __shared__ float s_g[BS][kOtfGStride];
   otf_tile<KIND, TPT, BS>(src, g, npad, B, chunk, pp, part, blockIdx.x, blockIdx.y, blockIdx.z * BS, s_src, s_g);
 }
 

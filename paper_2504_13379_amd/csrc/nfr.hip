@@ -261,7 +261,13 @@ struct OtfPlan {
 // States per block of the on-the-fly pair sum: one kernel evaluation serves
 // every state of a block, so larger blocks cost fewer evaluations per pair
 // interaction; targets per thread shrink as blocks grow (registers).
-int otf_bs(int B) { return B == 1 ? 1 : (B == 2 ? 2 : (B <= 4 ? 4 : (B <= 8 ? 8 : 16))); }
+// From 9 states on the products run on the matrix cores (k_otf_mfma_sum), in as
+// few blocks of up to 64 states as possible, of equal numbers of 16.
+int otf_bs(int B) {
+  if (B <= 8) return B == 1 ? 1 : (B == 2 ? 2 : (B <= 4 ? 4 : 8));
+  return 16 * (int)ceil_div(ceil_div(B, 16), ceil_div(B, 64));
+}
+int64_t otf_tile_targets(int bs) { return (int64_t)kWG * (bs > 8 ? 1 : otf_tpt(bs)); }
 
 // Tuned workgroup targets of the multi-state on-the-fly pair sum (its one
 // free launch parameter: how many source chunks the work is cut into), keyed
@@ -289,12 +295,28 @@ int64_t otf_target_wgs(int64_t npad, int B) {
   return best;
 }
 
+// Slots that a target of workgroups gives with blocks of 16 states on the vector
+// units (512 targets per workgroup, 1024 up to 4 states): the split of the
+// first version, whose workspace sizes bound the present plan's.
+int64_t otf_base_split(int64_t npad, int B, int64_t target) {
+  const int64_t tiles = ceil_div(npad, (int64_t)kWG * (B <= 4 ? 4 : 2)) * ceil_div(B, 16);
+  const int64_t want = std::min(std::max<int64_t>(ceil_div(target, tiles), 1), npad / kWG);
+  return ceil_div(npad, round_up(ceil_div(npad, want), kWG));
+}
+
+// Two workgroups per target of the tune table: with 2048 the last ones leave
+// less of the chip idle (N = 20011, 16 states: 282 against 296 us per
+// application; 7 states 224 / 238, 2 states 183 / 204).  More slots would let
+// nfr_apply_noalloc refuse a problem that it took before: then as before.
 OtfPlan plan_otf_target(int64_t npad, int B, int64_t target) {
   OtfPlan p;
   p.bs = otf_bs(B);
   p.nsb = (int)ceil_div(B, p.bs);
-  p.tiles = ceil_div(npad, (int64_t)kWG * otf_tpt(p.bs));
-  int64_t want = ceil_div(target, p.tiles * p.nsb);
+  p.tiles = ceil_div(npad, otf_tile_targets(p.bs));
+  int64_t want = ceil_div(2 * target, p.tiles * p.nsb);
+  const int64_t slot = (int64_t)B * npad * 8, base = otf_base_split(npad, B, target);
+  const int64_t room = ((int64_t)NFR_APPLY_NOALLOC_MAX_BYTES - 512 - npad * B * 4) / slot;
+  if (base <= room && want > room) want = std::max(base, room);
   const int64_t max_split = npad / kWG;
   if (want < 1) want = 1;
   if (want > max_split) want = max_split;
@@ -467,8 +489,14 @@ void launch_otf_kind(const ProblemView& pv, const PairParams& pp, int B, const f
     hipLaunchKernelGGL((k_otf_pair_sum<KIND, otf_tpt(4), 4>), grid, dim3(kWG), 0, s, pv.src, g, pv.npad, B, pl.chunk, pp, part);
   else if (pl.bs == 8)
     hipLaunchKernelGGL((k_otf_pair_sum<KIND, otf_tpt(8), 8>), grid, dim3(kWG), 0, s, pv.src, g, pv.npad, B, pl.chunk, pp, part);
+  else if (pl.bs == 16)
+    hipLaunchKernelGGL((k_otf_mfma_sum<KIND, 1>), grid, dim3(kWG), 0, s, pv.src, g, pv.npad, B, pl.chunk, pp, part);
+  else if (pl.bs == 32)
+    hipLaunchKernelGGL((k_otf_mfma_sum<KIND, 2>), grid, dim3(kWG), 0, s, pv.src, g, pv.npad, B, pl.chunk, pp, part);
+  else if (pl.bs == 48)
+    hipLaunchKernelGGL((k_otf_mfma_sum<KIND, 3>), grid, dim3(kWG), 0, s, pv.src, g, pv.npad, B, pl.chunk, pp, part);
   else
-    hipLaunchKernelGGL((k_otf_pair_sum<KIND, otf_tpt(16), 16>), grid, dim3(kWG), 0, s, pv.src, g, pv.npad, B, pl.chunk, pp, part);
+    hipLaunchKernelGGL((k_otf_mfma_sum<KIND, 4>), grid, dim3(kWG), 0, s, pv.src, g, pv.npad, B, pl.chunk, pp, part);
 }
 
 void launch_gemv(const ProblemView& pv, const float* W, int B, const float* G, double* part, const GemvPlan& pl,
@@ -2301,7 +2329,7 @@ int nfr_tune(nfr_context* ctx, const char* cache_path, int64_t n_max, int B_max,
       int64_t last_split = -1;
       for (int64_t target : kTuneTargets) {
         const OtfPlan pl = plan_otf_target(pv.npad, B, target);
-        if (pl.nsplit > kTuneMaxSplit || pl.nsplit == last_split) continue;   // same launch as the previous target
+        if ((int64_t)pl.nsplit * B > (int64_t)kTuneMaxSplit * std::min(B_max, 256) || pl.nsplit == last_split) continue;   // same launch as the previous target
         last_split = pl.nsplit;
         launch_otf_kind<0>(pv, pp, B, g, part, pl, s);
         NFR_HIP(hipEventRecord(ev0, s));
