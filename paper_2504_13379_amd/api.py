@@ -18,14 +18,29 @@ def _ptr(t) -> int | None:
     return None if t is None else t.data_ptr()
 
 
+def _on_stream(stream: torch.cuda.Stream, fn):
+    """fn() with `stream` current.  torch.cuda.stream() costs 6 us a use, which
+    a small call feels; setting and restoring the stream costs 2."""
+    if torch.cuda.current_device() != stream.device_index:
+        with torch.cuda.stream(stream):
+            return fn()
+    cur = torch.cuda.current_stream()
+    if cur == stream:
+        return fn()
+    torch.cuda.set_stream(stream)
+    try:
+        return fn()
+    finally:
+        torch.cuda.set_stream(cur)
+
+
 def _dev_buffer(nbytes: int, device, stream: torch.cuda.Stream | None = None) -> torch.Tensor:
     """256-byte aligned device bytes.  With `stream`, the block is allocated while
     that stream is current, so torch's caching allocator orders its reuse after
     the work the library enqueues there (the library runs on the context's
     stream, which need not be the caller's current stream)."""
     if stream is not None:
-        with torch.cuda.stream(stream):
-            return _dev_buffer(nbytes, device)
+        return _on_stream(stream, lambda: _dev_buffer(nbytes, device))
     buf = torch.empty(max(int(nbytes), 1) + 256, dtype=torch.uint8, device=device)
     off = (-buf.data_ptr()) % 256
     return buf[off:off + max(int(nbytes), 1)]
@@ -62,6 +77,7 @@ class Context:
     def __init__(self, device: int = 0, stream: torch.cuda.Stream | None = None):
         self.device = torch.device("cuda", device)
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
+        self._events = []                # idle events of order_after_caller
         h = c_void_p()
         L.check(L.lib().nfr_context_create(device, c_void_p(self.stream.cuda_stream), byref(h)))
         self.handle = h
@@ -73,7 +89,16 @@ class Context:
         a caller on another stream waits for it before reading them."""
         cur = torch.cuda.current_stream(self.device)
         if cur != self.stream:
-            self.stream.wait_stream(cur)
+            # a wait holds the event's state as of its call, so the event is free
+            # again after it; a call takes one off the list, so threads never share
+            try:
+                ev = self._events.pop()
+            except IndexError:
+                ev = torch.cuda.Event()
+            ev.record(cur)
+            self.stream.wait_event(ev)
+            if len(self._events) < 8:
+                self._events.append(ev)
 
     @property
     def arch(self) -> str:
@@ -150,12 +175,10 @@ class Problem:
     def apply(self, kernel: L.NfrKernel, firing: Firing, u: torch.Tensor, form: int = L.FORM_ONTHEFLY_FP32,
               W: torch.Tensor | None = None, out: torch.Tensor | None = None) -> torch.Tensor:
         B = self._check_state(u)
-        if out is None:
-            with torch.cuda.stream(self.ctx.stream):
-                out = torch.empty_like(u)
-        y = out
         ws_bytes = L.lib().nfr_apply_workspace_size(self.handle, B, form)
-        ws = _dev_buffer(ws_bytes, self.ctx.device, self.ctx.stream)
+        out, ws = _on_stream(self.ctx.stream, lambda: (torch.empty_like(u) if out is None else out,
+                                                       _dev_buffer(ws_bytes, self.ctx.device)))
+        y = out
         fs = firing.struct(self.ctx.device)
         self.ctx.order_after_caller()
         L.check(L.lib().nfr_apply(self.handle, byref(kernel), byref(fs), B, u.data_ptr(), y.data_ptr(), form,

@@ -739,7 +739,7 @@ __global__ __launch_bounds__(kWG) void k_otf_small(const float4* __restrict__ sr
     for (int w = 0; w < kWG / 64; ++w) y += red[w][threadIdx.x];
     const int64_t i = r0 + threadIdx.x;
     if (!STAGE) {
-      part[i] = pp.amp * y;
+      if (i < n) part[i] = 0.0 + pp.amp * y;   // the single slot's total
     } else if (updater) {
       double ys = 0.0;            // as slot_total adds the single slot
       ys += pp.amp * y;

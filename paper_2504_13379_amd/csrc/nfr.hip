@@ -1115,6 +1115,12 @@ int apply_launch(nfr_problem* prob, const nfr_kernel* kernel, const nfr_firing* 
     y_out = w.yt;
   }
   if ((st = launch_prep(pv, form, B, u_in, fr, w, nullptr, s))) return st;
+  if (use_small_stage(pv, form, B)) {
+    // the one-sided kernel's single slot is the result
+    Workspace direct = w;
+    direct.part = y_out;
+    return launch_pairs(prob->ctx, pv, *kernel, form, B, w_dev, direct);
+  }
   if ((st = launch_pairs(prob->ctx, pv, *kernel, form, B, w_dev, w))) return st;
   const int nsplit = w.nsplit;
   const int64_t total = pv.n * (int64_t)B;
