@@ -65,15 +65,17 @@ struct QuadGrid {
   int nx, ny, nz;
 };
 
-// One workgroup of kWG threads: bounding box of the nodes, then (thread 0) a
+// One workgroup of kGridThreads threads (256 took 71 us at N = 65538, waiting for
+// loads): bounding box of the nodes, then (thread 0) a
 // grid with about 4 nodes per cell of the box's volume (a surface fills a
 // small share of its box, so occupied cells hold a few tens of nodes), at most
 // max_cells cells.
-__global__ __launch_bounds__(kWG) void k_quad_grid(const double* __restrict__ xyz, int64_t n, int64_t max_cells,
+constexpr int kGridThreads = 1024;
+__global__ __launch_bounds__(kGridThreads) void k_quad_grid(const double* __restrict__ xyz, int64_t n, int64_t max_cells,
                                                    QuadGrid* __restrict__ grid) {
-  __shared__ double s_lo[3][kWG], s_hi[3][kWG];
+  __shared__ double s_lo[3][kGridThreads], s_hi[3][kGridThreads];
   double lo[3] = {xyz[0], xyz[1], xyz[2]}, hi[3] = {xyz[0], xyz[1], xyz[2]};
-  for (int64_t i = threadIdx.x; i < n; i += kWG)
+  for (int64_t i = threadIdx.x; i < n; i += kGridThreads)
     for (int d = 0; d < 3; ++d) {
       lo[d] = fmin(lo[d], xyz[3 * i + d]);
       hi[d] = fmax(hi[d], xyz[3 * i + d]);
@@ -83,7 +85,7 @@ __global__ __launch_bounds__(kWG) void k_quad_grid(const double* __restrict__ xy
     s_hi[d][threadIdx.x] = hi[d];
   }
   __syncthreads();
-  for (int w = kWG / 2; w > 0; w >>= 1) {
+  for (int w = kGridThreads / 2; w > 0; w >>= 1) {
     if (threadIdx.x < w)
       for (int d = 0; d < 3; ++d) {
         s_lo[d][threadIdx.x] = fmin(s_lo[d][threadIdx.x], s_lo[d][threadIdx.x + w]);
@@ -152,20 +154,15 @@ __global__ __launch_bounds__(kWG) void k_quad_bin_fill(const double* __restrict_
 
 __device__ inline bool key_less(double d, int i, double d2, int i2) { return d < d2 || (d == d2 && i < i2); }
 
-// st[t*k + r], r < k: the k nodes with the smallest (squared distance, index)
-// to centroid t, in increasing order; one wave per centroid.  Lane r holds
-// entry r of the sorted list; a candidate below the k-th key is inserted by a
-// ballot (its rank) and a one-lane shift.  cnt / start: nodes per cell and
-// their offsets into `nodes`.  Requires k <= 64 and k <= n.
-__global__ __launch_bounds__(kWG) void k_quad_knn(const double* __restrict__ xyz, const QuadGrid* __restrict__ grid_p,
-                                                  const int* __restrict__ cnt, const int64_t* __restrict__ start,
-                                                  const int* __restrict__ nodes, const double* __restrict__ cen,
-                                                  int64_t ntri, int k, int* __restrict__ st) {
-  const int lane = threadIdx.x & 63;
-  const int64_t t = (int64_t)blockIdx.x * (kWG / 64) + (threadIdx.x >> 6);
-  if (t >= ntri) return;
-  const QuadGrid g = *grid_p;
-  const double cx = cen[3 * t], cy = cen[3 * t + 1], cz = cen[3 * t + 2];
+// The k nodes with the smallest (squared distance, index) to the point c, in
+// increasing order, entry r in lane r (one wave): rings of cells visited one
+// cell after the other, the sorted list held one entry per lane; a candidate
+// below the k-th key is inserted by a ballot (its rank) and a one-lane shift.
+// Serves what quad_knn_select leaves (grids of few cells, clustered or
+// coincident nodes).
+__device__ inline int quad_knn_scan(const double* __restrict__ xyz, const QuadGrid& g, const int* __restrict__ cnt,
+                                    const int64_t* __restrict__ start, const int* __restrict__ nodes, double cx,
+                                    double cy, double cz, int k, int lane) {
   const int ix = quad_cell_coord(cx, g.ox, g.h, g.nx);
   const int iy = quad_cell_coord(cy, g.oy, g.h, g.ny);
   const int iz = quad_cell_coord(cz, g.oz, g.h, g.nz);
@@ -231,7 +228,170 @@ __global__ __launch_bounds__(kWG) void k_quad_knn(const double* __restrict__ xyz
     if (bound == __builtin_inf()) break;                                   // every cell visited
     if (thr_i != 0x7fffffff && bound > 0.0 && thr < bound * bound * (1.0 - 1e-12)) break;
   }
-  if (lane < k) st[t * k + lane] = li;
+  return li;
+}
+
+// The same by selection; returns false where it does not apply.  The nodes of
+// the (2 r + 1)^2 rows of cells around c (a row's cells are consecutive in the
+// cell order, so its nodes are one run of `nodes`) are flattened over the lanes,
+// up to kKnnHeld per lane; when at least k keys lie below the squared distance
+// to the rows' boundary, a threshold with k to 64 keys below it is found by
+// counting ballots (keys of a surface's nodes are about evenly spread, so
+// interpolation hits within a few tries), and those keys are sorted.
+constexpr int kKnnHeld = 8;
+struct KnnScratch {
+  double key[64];
+  int idx[64], pre[64], beg[64];
+};
+
+__device__ inline bool quad_knn_select(const double* __restrict__ xyz, const QuadGrid& g, const int* __restrict__ cnt,
+                                       const int64_t* __restrict__ start, const int* __restrict__ nodes, double cx,
+                                       double cy, double cz, int k, int lane, KnnScratch& s, int* out) {
+  const int ix = quad_cell_coord(cx, g.ox, g.h, g.nx);
+  const int iy = quad_cell_coord(cy, g.oy, g.h, g.ny);
+  const int iz = quad_cell_coord(cz, g.oz, g.h, g.nz);
+  for (int r = 1; r <= 3; ++r) {
+    const int side = 2 * r + 1;
+    int beg = 0, len = 0;
+    {
+      const int y = iy + lane % side - r, z = iz + lane / side - r;
+      if (lane < side * side && y >= 0 && y < g.ny && z >= 0 && z < g.nz) {
+        const int64_t c = ((int64_t)z * g.ny + y) * g.nx;
+        const int x0 = max(ix - r, 0), x1 = min(ix + r, g.nx - 1);
+        beg = (int)start[c + x0];
+        len = (int)start[c + x1] + cnt[c + x1] - beg;
+      }
+    }
+    int pre = len;   // inclusive prefix sum over the rows
+    for (int o = 1; o < 64; o *= 2) {
+      const int v = __shfl_up(pre, o);
+      if (lane >= o) pre += v;
+    }
+    const int total = __builtin_amdgcn_readlane(pre, 63);
+    if (total > 64 * kKnnHeld) return false;
+    double bound = __builtin_inf();   // distance to the nearest side with cells beyond it
+    const double o[3] = {g.ox, g.oy, g.oz};
+    const double p[3] = {cx, cy, cz};
+    const int ic[3] = {ix, iy, iz};
+    const int dims[3] = {g.nx, g.ny, g.nz};
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      if (ic[d] - r > 0) bound = fmin(bound, p[d] - (o[d] + (double)(ic[d] - r) * g.h));
+      if (ic[d] + r < dims[d] - 1) bound = fmin(bound, (o[d] + (double)(ic[d] + r + 1) * g.h) - p[d]);
+    }
+    if (bound == __builtin_inf()) return false;
+    if (total < k || !(bound > 0.0)) continue;
+    const double b2 = bound * bound * (1.0 - 1e-12);
+
+    s.pre[lane] = pre;
+    s.beg[lane] = beg - (pre - len);
+    __builtin_amdgcn_wave_barrier();
+    double key[kKnnHeld];
+    int idx[kKnnHeld];
+#pragma unroll
+    for (int q = 0; q < kKnnHeld; ++q) {
+      key[q] = __builtin_inf();
+      idx[q] = 0;
+      if (64 * q >= total) continue;
+      const int e = 64 * q + lane;
+      int row = 0;             // first row whose prefix exceeds e
+#pragma unroll
+      for (int w = 32; w > 0; w /= 2)
+        if (s.pre[row + w - 1] <= e) row += w;
+      if (e < total) {
+        const int j = nodes[s.beg[row] + e];
+        idx[q] = j;
+        key[q] = quad_sqdist(xyz[3 * (int64_t)j], xyz[3 * (int64_t)j + 1], xyz[3 * (int64_t)j + 2], cx, cy, cz);
+      }
+    }
+    auto below = [&](double t) {
+      int c = 0;
+#pragma unroll
+      for (int q = 0; q < kKnnHeld; ++q)
+        if (64 * q < total) c += __popcll(__ballot(key[q] < t));
+      return c;
+    };
+    double t = b2, t_lo = 0.0;
+    int c = below(t), c_lo = 0;
+    if (c < k) continue;
+    if (c > 64) {
+      double t_hi = t;
+      int c_hi = c, tries = 0;
+      const double want = 0.5 * (k + 64);
+      for (;; ++tries) {
+        if (tries == 40) return false;        // equal keys
+        const double f = tries < 8 ? (want - c_lo) / (double)(c_hi - c_lo) : 0.5;
+        t = t_lo + (t_hi - t_lo) * f;
+        c = below(t);
+        if (c < k) {
+          t_lo = t;
+          c_lo = c;
+        } else if (c > 64) {
+          t_hi = t;
+          c_hi = c;
+        } else {
+          break;
+        }
+      }
+    }
+    s.key[lane] = __builtin_inf();
+    s.idx[lane] = 0x7fffffff;
+    __builtin_amdgcn_wave_barrier();
+    int base = 0;
+#pragma unroll
+    for (int q = 0; q < kKnnHeld; ++q) {
+      if (64 * q >= total) continue;
+      const bool in = key[q] < t;
+      const uint64_t mask = __ballot(in);
+      const int at = base + __popcll(mask & ((1ull << lane) - 1));
+      if (in) {
+        s.key[at] = key[q];
+        s.idx[at] = idx[q];
+      }
+      base += __popcll(mask);
+    }
+    __builtin_amdgcn_wave_barrier();
+    double d = s.key[lane];
+    int i = s.idx[lane];
+    __builtin_amdgcn_wave_barrier();
+    for (int w = 2; w <= 64; w *= 2)          // bitonic sort of the 64 (key, index)
+      for (int j = w / 2; j > 0; j /= 2) {
+        const double pd = __shfl_xor(d, j);
+        const int pi = __shfl_xor(i, j);
+        const bool up = (lane & w) == 0, low = (lane & j) == 0;
+        const bool take = key_less(pd, pi, d, i) == (up == low);
+        d = take ? pd : d;
+        i = take ? pi : i;
+      }
+    *out = i;
+    return true;
+  }
+  return false;
+}
+
+// st[t*k + r], r < k: the stencil of triangle t (one wave); rank[t*k + r]: the
+// entry's place among its node's entries, in the order in which they arrive.
+// cnt / start: nodes per cell and their offsets into `nodes`.  Requires k <= 64
+// and k <= n.  N = 65538, k = 32: 230 us; 930 us by quad_knn_scan alone, whose
+// cells and insertions follow one another.
+__global__ __launch_bounds__(kWG) void k_quad_knn(const double* __restrict__ xyz, const QuadGrid* __restrict__ grid_p,
+                                                  const int* __restrict__ cnt, const int64_t* __restrict__ start,
+                                                  const int* __restrict__ nodes, const double* __restrict__ cen,
+                                                  int64_t n, int64_t ntri, int k, int* __restrict__ st,
+                                                  int* __restrict__ node_cnt, int* __restrict__ rank) {
+  __shared__ KnnScratch scratch[kWG / 64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t t = (int64_t)blockIdx.x * (kWG / 64) + wave;
+  if (t >= ntri) return;
+  const QuadGrid g = *grid_p;
+  const double cx = cen[3 * t], cy = cen[3 * t + 1], cz = cen[3 * t + 2];
+  int li;
+  if (!quad_knn_select(xyz, g, cnt, start, nodes, cx, cy, cz, k, lane, scratch[wave], &li))
+    li = quad_knn_scan(xyz, g, cnt, start, nodes, cx, cy, cz, k, lane);
+  if (lane >= k) return;
+  st[t * k + lane] = li;
+  if (li >= 0 && li < n) rank[t * k + lane] = atomicAdd(&node_cnt[li], 1);
 }
 
 // ------------------------------------------------------------------ projection points
@@ -434,7 +594,8 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
 }
 
 // One wave per triangle t: pull-back, Jacobian, planar system, LU with partial
-// pivoting, back substitution; wE[t*k + r] = w_r h_t^2 J_r.
+// pivoting, back substitution; entry e = t*k + r gives w_r h_t^2 J_r to its node's
+// list (place off[node] + rank[e]).
 //
 // Lane r holds row r of the (k+6) x (k+6) system and its right-hand side in
 // registers, with the kernel columns at 0 .. k-1 and the polynomial columns at
@@ -453,7 +614,9 @@ __global__ __launch_bounds__(64) void k_quad_elements(const double* __restrict__
                                                       const int* __restrict__ tri, const double* __restrict__ cen,
                                                       const double* __restrict__ nrm_tri,
                                                       const double* __restrict__ proj, const int* __restrict__ st,
-                                                      int64_t n, int64_t ntri, int k, double* __restrict__ wE) {
+                                                      int64_t n, int64_t ntri, int k, const int64_t* __restrict__ off,
+                                                      const int* __restrict__ rank, double* __restrict__ val,
+                                                      int* __restrict__ list) {
   constexpr int D = KP + 6;
   __shared__ double s_poly[6][KP];     // polynomial rows (the transposed polynomial columns)
   const int dim = k + 6;
@@ -610,18 +773,18 @@ __global__ __launch_bounds__(64) void k_quad_elements(const double* __restrict__
     rhs = fma(-a[col], xc, rhs);
     w = lane == col ? xc : w;
   }
-  if (lane < k) wE[t * k + lane] = w * h * h * J;
+  if (lane < k) {
+    const int64_t e = t * k + lane;
+    const int i = st[e];
+    if (i >= 0 && i < n) {
+      const int64_t at = off[i] + rank[e];
+      val[at] = w * h * h * J;
+      list[at] = (int)e;
+    }
+  }
 }
 
 // ------------------------------------------------------------------ accumulation
-
-__global__ __launch_bounds__(kWG) void k_quad_count(const int* __restrict__ st, int64_t total, int64_t n,
-                                                    int* __restrict__ cnt) {
-  const int64_t e = (int64_t)blockIdx.x * kWG + threadIdx.x;
-  if (e >= total) return;
-  const int i = st[e];
-  if (i >= 0 && i < n) atomicAdd(&cnt[i], 1);
-}
 
 // Exclusive prefix sums in three passes: block totals, a single-workgroup
 // scan of the totals, then each block's own scan plus its offset.
@@ -674,39 +837,60 @@ __global__ __launch_bounds__(kWG) void k_scan_apply(const int* __restrict__ cnt,
   if (i < n) off[i] = bsum[blockIdx.x] + s[threadIdx.x] - v;
 }
 
-// Entry e = t*k + r of the stencil table goes to a free place in its node's
-// segment (the order inside a segment is fixed afterwards by sorting).
-__global__ __launch_bounds__(kWG) void k_quad_fill(const int* __restrict__ st, int64_t total, int64_t n,
-                                                   const int64_t* __restrict__ off, int* __restrict__ cursor,
-                                                   int* __restrict__ list) {
-  const int64_t e = (int64_t)blockIdx.x * kWG + threadIdx.x;
-  if (e >= total) return;
-  const int i = st[e];
-  if (i < 0 || i >= n) return;
-  list[off[i] + atomicAdd(&cursor[i], 1)] = (int)e;
-}
-
-// q_i = sum of wE over node i's segment in increasing entry order (insertion
-// sort of the segment first).
+// q_i = sum of node i's entries in a fixed order of their numbers, one wave per
+// node: up to kSumHeld entries are put in increasing order through LDS by their
+// rank among the others and added by a fixed tree; longer lists (never a mesh
+// of bounded valence) in increasing order, one after the other.  A thread per
+// node sorting its list in memory took 490 us at N = 65538, a wave 58.
+constexpr int kSumHeld = 256;
 __global__ __launch_bounds__(kWG) void k_quad_sum(const int64_t* __restrict__ off, const int* __restrict__ cnt,
-                                                  int64_t n, int* __restrict__ list, const double* __restrict__ wE,
-                                                  double* __restrict__ q) {
-  const int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x;
+                                                  int64_t n, const int* __restrict__ list,
+                                                  const double* __restrict__ val, double* __restrict__ q) {
+  __shared__ double s_val[kWG / 64][kSumHeld];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t i = (int64_t)blockIdx.x * (kWG / 64) + wave;
   if (i >= n) return;
-  int* seg = list + off[i];
-  const int len = cnt[i];
-  for (int a = 1; a < len; ++a) {
-    const int key = seg[a];
-    int b = a - 1;
-    while (b >= 0 && seg[b] > key) {
-      seg[b + 1] = seg[b];
-      --b;
-    }
-    seg[b + 1] = key;
-  }
+  const int len = __builtin_amdgcn_readfirstlane(cnt[i]);
+  const int* const seg = list + off[i];
+  const double* const v = val + off[i];
   double acc = 0.0;
-  for (int a = 0; a < len; ++a) acc += wE[seg[a]];
-  q[i] = acc;
+  if (len <= kSumHeld) {
+    int e[kSumHeld / 64];
+#pragma unroll
+    for (int c = 0; c < kSumHeld / 64; ++c) e[c] = 64 * c + lane < len ? seg[64 * c + lane] : 0x7fffffff;
+    for (int c = 0; 64 * c < len; ++c) {
+      const int mine = 64 * c + lane < len ? seg[64 * c + lane] : 0x7fffffff;
+      int r = 0;
+#pragma unroll
+      for (int d = 0; d < kSumHeld / 64; ++d)
+        for (int b = 0; b < 64 && 64 * d + b < len; ++b) r += __builtin_amdgcn_readlane(e[d], b) < mine ? 1 : 0;
+      if (64 * c + lane < len) s_val[wave][r] = v[64 * c + lane];
+    }
+    __builtin_amdgcn_wave_barrier();
+    for (int c = lane; c < len; c += 64) acc += s_val[wave][c];
+    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+  } else {
+    int last = -1;
+    for (int a = 0; a < len; ++a) {
+      int best = 0x7fffffff, at = 0;
+      for (int c = lane; c < len; c += 64)
+        if (seg[c] > last && seg[c] < best) {
+          best = seg[c];
+          at = c;
+        }
+      for (int o = 32; o > 0; o >>= 1) {
+        const int ob = __shfl_xor(best, o), oa = __shfl_xor(at, o);
+        if (ob < best) {
+          best = ob;
+          at = oa;
+        }
+      }
+      acc += v[at];
+      last = best;
+    }
+  }
+  if (lane == 0) q[i] = acc;
 }
 
 }  // namespace nfr

@@ -2010,9 +2010,9 @@ struct QuadWorkspace {
   double* nrm_tri = nullptr;
   double* proj = nullptr;
   int* st = nullptr;
-  double* wE = nullptr;
-  int* cnt = nullptr;
-  int* cursor = nullptr;
+  int* rank = nullptr;        // of every stencil entry among its node's
+  double* val = nullptr;      // the entries' weights, grouped by node
+  int* cnt = nullptr;         // entries per node; cnt, gcnt and gcursor are adjacent and cleared together
   int64_t* off = nullptr;
   int64_t* bsum = nullptr;
   int* list = nullptr;
@@ -2043,14 +2043,14 @@ QuadWorkspace carve_quad(void* base, int64_t n, int64_t ntri, int k) {
   w.nrm_tri = static_cast<double*>(take(3 * size_t(ntri) * sizeof(double)));
   w.proj = static_cast<double*>(take(3 * size_t(ntri) * sizeof(double)));
   w.st = static_cast<int*>(take(tk * sizeof(int)));
-  w.wE = static_cast<double*>(take(tk * sizeof(double)));
-  w.cnt = static_cast<int*>(take(size_t(n) * sizeof(int)));
-  w.cursor = static_cast<int*>(take(size_t(n) * sizeof(int)));
+  w.val = static_cast<double*>(take(tk * sizeof(double)));
+  w.rank = static_cast<int*>(take(tk * sizeof(int)));
   w.off = static_cast<int64_t*>(take(size_t(n) * sizeof(int64_t)));
   w.bsum = static_cast<int64_t*>(take(size_t(ceil_div(n, kWG)) * sizeof(int64_t)));
   w.list = static_cast<int*>(take(tk * sizeof(int)));
   const int64_t mc = quad_max_cells(n);
   w.grid = static_cast<QuadGrid*>(take(sizeof(QuadGrid)));
+  w.cnt = static_cast<int*>(take(size_t(n) * sizeof(int)));
   w.gcnt = static_cast<int*>(take(size_t(mc) * sizeof(int)));
   w.gcursor = static_cast<int*>(take(size_t(mc) * sizeof(int)));
   w.gstart = static_cast<int64_t*>(take(size_t(mc) * sizeof(int64_t)));
@@ -2140,15 +2140,12 @@ int nfr_quad_weights(nfr_context* ctx, int64_t n, const double* xyz_dev, const d
   hipStream_t s = ctx->stream;
   int* stn = stencil_dev ? stencil_dev : w.st;
   double* proj = proj_dev ? proj_dev : w.proj;
-  const size_t tk = size_t(ntri) * k;
   NFR_HIP(hipMemcpyAsync(w.tri, tri_host, 3 * size_t(ntri) * sizeof(int), hipMemcpyHostToDevice, s));
   if (planes)
     NFR_HIP(hipMemcpyAsync(w.nbr, nbr.data(), 3 * size_t(ntri) * sizeof(int), hipMemcpyHostToDevice, s));
-  NFR_HIP(hipMemsetAsync(w.cnt, 0, size_t(n) * sizeof(int), s));
-  NFR_HIP(hipMemsetAsync(w.cursor, 0, size_t(n) * sizeof(int), s));
   const int64_t mc = quad_max_cells(n);
-  NFR_HIP(hipMemsetAsync(w.gcnt, 0, size_t(mc) * sizeof(int), s));
-  NFR_HIP(hipMemsetAsync(w.gcursor, 0, size_t(mc) * sizeof(int), s));
+  const int64_t clear = (int64_t)((reinterpret_cast<char*>(w.gstart) - reinterpret_cast<char*>(w.cnt)) / sizeof(double));
+  hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)ceil_div(clear, kWG)), dim3(kWG), 0, s, reinterpret_cast<double*>(w.cnt), clear);
   const unsigned tb = (unsigned)ceil_div(ntri, kWG);
   hipLaunchKernelGGL(k_quad_centroids, dim3(tb), dim3(kWG), 0, s, xyz_dev, w.tri, ntri, w.cen, w.nrm_tri);
   hipLaunchKernelGGL(k_quad_proj, dim3(tb), dim3(kWG), 0, s, xyz_dev, w.tri, w.nbr, w.cen, w.nrm_tri, ntri,
@@ -2156,31 +2153,29 @@ int nfr_quad_weights(nfr_context* ctx, int64_t n, const double* xyz_dev, const d
   // k nearest nodes: bin the nodes into a grid, then search rings of cells
   const unsigned nbn = (unsigned)ceil_div(n, kWG);
   const int64_t nbc = ceil_div(mc, kWG);
-  hipLaunchKernelGGL(k_quad_grid, dim3(1), dim3(kWG), 0, s, xyz_dev, n, mc, w.grid);
+  hipLaunchKernelGGL(k_quad_grid, dim3(1), dim3(kGridThreads), 0, s, xyz_dev, n, mc, w.grid);
   hipLaunchKernelGGL(k_quad_bin_count, dim3(nbn), dim3(kWG), 0, s, xyz_dev, n, w.grid, w.gcnt);
   hipLaunchKernelGGL(k_scan_blocks, dim3((unsigned)nbc), dim3(kWG), 0, s, w.gcnt, mc, w.gbsum);
   hipLaunchKernelGGL(k_scan_totals, dim3(1), dim3(kWG), 0, s, w.gbsum, nbc);
   hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nbc), dim3(kWG), 0, s, w.gcnt, mc, w.gbsum, w.gstart);
   hipLaunchKernelGGL(k_quad_bin_fill, dim3(nbn), dim3(kWG), 0, s, xyz_dev, n, w.grid, w.gstart, w.gcursor, w.gnodes);
   hipLaunchKernelGGL(k_quad_knn, dim3((unsigned)ceil_div(ntri, kWG / 64)), dim3(kWG), 0, s, xyz_dev, w.grid, w.gcnt,
-                     w.gstart, w.gnodes, w.cen, ntri, k, stn);
+                     w.gstart, w.gnodes, w.cen, n, ntri, k, stn, w.cnt, w.rank);
+  // places of every node's entries
+  const int64_t nb = ceil_div(n, kWG);
+  hipLaunchKernelGGL(k_scan_blocks, dim3((unsigned)nb), dim3(kWG), 0, s, w.cnt, n, w.bsum);
+  hipLaunchKernelGGL(k_scan_totals, dim3(1), dim3(kWG), 0, s, w.bsum, nb);
+  hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb), dim3(kWG), 0, s, w.cnt, n, w.bsum, w.off);
   // registers for the smallest of four sizes that holds k (32 is the default stencil)
 #define NFR_QUAD_ELEMENTS(KP)                                                                                     \
   hipLaunchKernelGGL(k_quad_elements<KP>, dim3((unsigned)ntri), dim3(64), 0, s, xyz_dev, nrm_dev, w.tri, w.cen, \
-                     w.nrm_tri, proj, stn, n, ntri, k, w.wE)
+                     w.nrm_tri, proj, stn, n, ntri, k, w.off, w.rank, w.val, w.list)
   if (k <= 20) NFR_QUAD_ELEMENTS(20);
   else if (k <= 32) NFR_QUAD_ELEMENTS(32);
   else if (k <= 45) NFR_QUAD_ELEMENTS(45);
   else NFR_QUAD_ELEMENTS(57);
 #undef NFR_QUAD_ELEMENTS
-  const unsigned eb = (unsigned)ceil_div((int64_t)tk, kWG);
-  const int64_t nb = ceil_div(n, kWG);
-  hipLaunchKernelGGL(k_quad_count, dim3(eb), dim3(kWG), 0, s, stn, (int64_t)tk, n, w.cnt);
-  hipLaunchKernelGGL(k_scan_blocks, dim3((unsigned)nb), dim3(kWG), 0, s, w.cnt, n, w.bsum);
-  hipLaunchKernelGGL(k_scan_totals, dim3(1), dim3(kWG), 0, s, w.bsum, nb);
-  hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb), dim3(kWG), 0, s, w.cnt, n, w.bsum, w.off);
-  hipLaunchKernelGGL(k_quad_fill, dim3(eb), dim3(kWG), 0, s, stn, (int64_t)tk, n, w.off, w.cursor, w.list);
-  hipLaunchKernelGGL(k_quad_sum, dim3((unsigned)nb), dim3(kWG), 0, s, w.off, w.cnt, n, w.list, w.wE, q_dev);
+  hipLaunchKernelGGL(k_quad_sum, dim3((unsigned)ceil_div(n, kWG / 64)), dim3(kWG), 0, s, w.off, w.cnt, n, w.list, w.val, q_dev);
   NFR_HIP_LAUNCH();
   return NFR_OK;
 }
