@@ -43,7 +43,7 @@ constexpr int kAdjThreads = 64 * kAdjSplit;
 template <int KIND, bool COLS>
 __device__ inline void sym_adj_tile(const float4* __restrict__ src, const float* __restrict__ lam, int64_t npad,
                                     int nt, const PairParams& pp, double* __restrict__ part, int64_t I, int64_t J,
-                                    double (*rowsum)[4][kSymTile]) {
+                                    double (*rowsum)[4][kSymTile], float4 (*srcs)[128]) {
   static_assert(kSymTile == 64 * kSymTPT, "one wave holds the tile's targets");
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -71,7 +71,7 @@ __device__ inline void sym_adj_tile(const float4* __restrict__ src, const float*
   for (int grp = wave; grp < ngroups; grp += kAdjSplit) {
     const int64_t j = J * kSymTile + grp * 64 + lane;
     const float4 s4 = src[j];
-    float sx = s4.x * pp.sig, sy = s4.y * pp.sig, sz = s4.z * pp.sig, sl = lam[j];
+    put_sources(srcs[wave], lane, make_float4(s4.x * pp.sig, s4.y * pp.sig, s4.z * pp.sig, lam[j]));
     float col[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     float acc[kSymTPT][4];
 #pragma unroll
@@ -80,9 +80,10 @@ __device__ inline void sym_adj_tile(const float4* __restrict__ src, const float*
       for (int c = 0; c < 4; ++c) acc[k][c] = 0.0f;
 #pragma unroll 2
     for (int step = 0; step < 64; ++step) {
+      const float4 q = srcs[wave][lane + 64 - step];
 #pragma unroll
       for (int k = 0; k < kSymTPT; ++k) {
-        const float r2 = pair_r2<KIND>(xi[k] - sx, yi[k] - sy, zi[k] - sz, pp.per);
+        const float r2 = pair_r2<KIND>(xi[k] - q.x, yi[k] - q.y, zi[k] - q.z, pp.per);
         const float t = ((KIND & 1) == 0) ? r2 : __builtin_amdgcn_sqrtf(r2);
         // with rho = 1/m the coordinates are in units of the inhibitory length
         // (t is the inhibitory argument; the combine scales T1, T2 by m)
@@ -90,10 +91,10 @@ __device__ inline void sym_adj_tile(const float4* __restrict__ src, const float*
         const float e1 = sym_pow<KIND>() == 0 ? __builtin_amdgcn_exp2f(-t) : ipow<sym_pow<KIND>()>(e2);
         const float e1t = e1 * t;
         const float e2t = e2 * t;
-        acc[k][0] = fmaf(e1, sl, acc[k][0]);
-        acc[k][1] = fmaf(e2, sl, acc[k][1]);
-        acc[k][2] = fmaf(e1t, sl, acc[k][2]);
-        acc[k][3] = fmaf(e2t, sl, acc[k][3]);
+        acc[k][0] = fmaf(e1, q.w, acc[k][0]);
+        acc[k][1] = fmaf(e2, q.w, acc[k][1]);
+        acc[k][2] = fmaf(e1t, q.w, acc[k][2]);
+        acc[k][3] = fmaf(e2t, q.w, acc[k][3]);
         if (COLS) {
           col[0] = fmaf(e1, li[k], col[0]);
           col[1] = fmaf(e2, li[k], col[1]);
@@ -101,10 +102,6 @@ __device__ inline void sym_adj_tile(const float4* __restrict__ src, const float*
           col[3] = fmaf(e2t, li[k], col[3]);
         }
       }
-      sx = wave_ror1(sx);
-      sy = wave_ror1(sy);
-      sz = wave_ror1(sz);
-      sl = wave_ror1(sl);
       if (COLS) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) col[c] = wave_ror1(col[c]);
@@ -153,12 +150,13 @@ __global__ __launch_bounds__(kAdjThreads) void k_sym_adjoint(const float4* __res
                                                              const float* __restrict__ lam, int64_t npad, int nt,
                                                              PairParams pp, double* __restrict__ part) {
   __shared__ double rowsum[kAdjSplit][4][kSymTile];
+  __shared__ float4 srcs[kAdjSplit][128];
   int64_t I, J;
   sym_decode(blockIdx.x, &I, &J);
   if (I == J)
-    sym_adj_tile<KIND, false>(src, lam, npad, nt, pp, part, I, J, rowsum);
+    sym_adj_tile<KIND, false>(src, lam, npad, nt, pp, part, I, J, rowsum, srcs);
   else
-    sym_adj_tile<KIND, true>(src, lam, npad, nt, pp, part, I, J, rowsum);
+    sym_adj_tile<KIND, true>(src, lam, npad, nt, pp, part, I, J, rowsum, srcs);
 }
 
 // Coefficients turning the raw sums into dw/dp terms:

@@ -412,10 +412,23 @@ __device__ inline void sym_decode(int64_t p, int64_t* I, int64_t* J) {
   *I = p - j * (j + 1) / 2;
 }
 
+// A wave's 64 sources (x, y, z, weight), stored twice over 128 places, so that
+// lane l's source after s rotations, (l - s) mod 64, is at place l + 64 - s: one
+// LDS read with a constant offset instead of four lane rotations.
+__device__ __forceinline__ void put_sources(float4* srcs, int lane, float4 v) {
+  __builtin_amdgcn_wave_barrier();   // the previous group's reads come first
+  srcs[lane] = v;
+  srcs[lane + 64] = v;
+  __builtin_amdgcn_wave_barrier();
+}
+#ifndef NFR_SYM_UNROLL
+#define NFR_SYM_UNROLL 4
+#endif
+
 template <int KIND, bool COLS, int TPT, int SPLIT>
 __device__ inline void sym_tile(const float4* __restrict__ src, const float* __restrict__ g, int64_t npad,
                                 const PairParams& pp, double* __restrict__ part, int64_t I, int64_t J,
-                                double (*rowsum)[64 * TPT]) {
+                                double (*rowsum)[64 * TPT], float4 (*srcs)[128]) {
   constexpr int kSymTPT = TPT, kSymSplit = SPLIT, kSymTile = 64 * TPT, kSymThreads = 64 * SPLIT;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -442,25 +455,22 @@ __device__ inline void sym_tile(const float4* __restrict__ src, const float* __r
   for (int grp = wave; grp < ngroups; grp += kSymSplit) {
     const int64_t j = J * kSymTile + grp * 64 + lane;
     const float4 s4 = src[j];
-    float sx = s4.x * pp.sig, sy = s4.y * pp.sig, sz = s4.z * pp.sig, sg = g[j];
+    put_sources(srcs[wave], lane, make_float4(s4.x * pp.sig, s4.y * pp.sig, s4.z * pp.sig, g[j]));
     float cs = 0.0f;
     float rs[kSymTPT];
 #pragma unroll
     for (int k = 0; k < kSymTPT; ++k) rs[k] = 0.0f;
-#pragma unroll 2
+#pragma unroll NFR_SYM_UNROLL
     for (int step = 0; step < 64; ++step) {
+      const float4 q = srcs[wave][lane + 64 - step];
 #pragma unroll
       for (int k = 0; k < kSymTPT; ++k) {
-        const float r2 = pair_r2<KIND>(xi[k] - sx, yi[k] - sy, zi[k] - sz, pp.per);
+        const float r2 = pair_r2<KIND>(xi[k] - q.x, yi[k] - q.y, zi[k] - q.z, pp.per);
         const float t = ((KIND & 1) == 0) ? r2 : __builtin_amdgcn_sqrtf(r2);
         const float u = pair_u<KIND>(t, rho, kappa);
-        rs[k] = fmaf(u, sg, rs[k]);
+        rs[k] = fmaf(u, q.w, rs[k]);
         if (COLS) cs = fmaf(u, gi[k], cs);
       }
-      sx = wave_ror1(sx);
-      sy = wave_ror1(sy);
-      sz = wave_ror1(sz);
-      sg = wave_ror1(sg);
       if (COLS) cs = wave_ror1(cs);
     }
 #pragma unroll
@@ -493,12 +503,13 @@ template <int KIND, int TPT, int SPLIT>
 __global__ __launch_bounds__(64 * SPLIT) void k_otf_sym(const float4* __restrict__ src, const float* __restrict__ g,
                                                         int64_t npad, PairParams pp, double* __restrict__ part) {
   __shared__ double rowsum[SPLIT][64 * TPT];
+  __shared__ float4 srcs[SPLIT][128];
   int64_t I, J;
   sym_decode(blockIdx.x, &I, &J);
   if (I == J)
-    sym_tile<KIND, false, TPT, SPLIT>(src, g, npad, pp, part, I, J, rowsum);
+    sym_tile<KIND, false, TPT, SPLIT>(src, g, npad, pp, part, I, J, rowsum, srcs);
   else
-    sym_tile<KIND, true, TPT, SPLIT>(src, g, npad, pp, part, I, J, rowsum);
+    sym_tile<KIND, true, TPT, SPLIT>(src, g, npad, pp, part, I, J, rowsum, srcs);
 }
 
 // ------------------------------------------------------------------ reductions
