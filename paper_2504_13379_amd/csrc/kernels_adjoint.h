@@ -78,7 +78,7 @@ __device__ inline void sym_adj_tile(const float4* __restrict__ src, const float*
     for (int k = 0; k < kSymTPT; ++k)
 #pragma unroll
       for (int c = 0; c < 4; ++c) acc[k][c] = 0.0f;
-#pragma unroll 2
+#pragma unroll 1
     for (int step = 0; step < 64; ++step) {
       const float4 q = srcs[wave][lane + 64 - step];
 #pragma unroll

@@ -421,8 +421,14 @@ __device__ __forceinline__ void put_sources(float4* srcs, int lane, float4 v) {
   srcs[lane + 64] = v;
   __builtin_amdgcn_wave_barrier();
 }
+// Steps per iteration of the rotation loops: one.  Its 49 instructions keep each
+// step's eight exponentials together and the waves out of step, and the vector
+// units issue 1.9 clocks per plain instruction beside them; with 2 or 4 steps
+// the scheduler spreads them and loses that (N = 65536, Gaussian: 618 us per
+// launch with 1, 747 with 2, 750 with 4; exponential 606 / 736 / 690; forcing an
+// exponential every five instructions 15 % slower than 4).
 #ifndef NFR_SYM_UNROLL
-#define NFR_SYM_UNROLL 4
+#define NFR_SYM_UNROLL 1
 #endif
 
 template <int KIND, bool COLS, int TPT, int SPLIT>
@@ -498,18 +504,145 @@ __device__ inline void sym_tile(const float4* __restrict__ src, const float* __r
   }
 }
 
+// Tile pairs of a launch that are split into their groups (sym_group): pairs
+// from `whole` on, whose extra slots take `rows` sets of three.
+struct SymRest {
+  unsigned whole;
+  int rows;
+};
+
+// Clears the extra slots of tile I that no split pair (I, J) fills: the set of
+// J = nt - 1 - r is filled for the pairs of the order from rest.whole on.
+__device__ inline void sym_clear_rest(const SymRest& rest, int64_t npad, int64_t I, double* __restrict__ part) {
+  const int64_t nt = npad / kSymTile;
+  for (int r = 0; r < rest.rows; ++r) {
+    const int64_t J = nt - 1 - r;
+    if (I <= J && J * (J + 1) / 2 + I >= (int64_t)rest.whole) continue;
+    for (int k = 0; k < 3; ++k) part[(nt + 3 * r + k) * npad + I * kSymTile + threadIdx.x] = 0.0;
+  }
+}
+
+constexpr int kSymRounds = 4;
+
+// One source group of a tile pair by the whole workgroup (SPLIT 4): in each of
+// kSymRounds rounds every wave evaluates the kernel for four consecutive steps
+// of the rotation (16 values, few enough that the kernel keeps 8 waves per
+// SIMD), then the waves add their values one after the other, handing the row
+// and column sums on through LDS.  The sums are those of a wave alone, bit for bit, in about a
+// third of its time; the last tile pairs of a launch run this way, so that it
+// does not end with a few waves at work for a whole group.
+template <int KIND, bool COLS>
+__device__ inline void sym_group(const float4* __restrict__ src, const float* __restrict__ g, int64_t npad,
+                                 const PairParams& pp, double* __restrict__ part, int64_t I, int64_t J, int grp,
+                                 int64_t slot, float4* srcs, float (*hand)[64]) {
+  // sym_tile's coordinates are rounded before they meet in the differences
+#pragma clang fp contract(off)
+  constexpr int TPT = kSymTPT, STEPS = 64 / kSymSplit / kSymRounds;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float xi[TPT], yi[TPT], zi[TPT], gi[TPT];
+#pragma unroll
+  for (int k = 0; k < TPT; ++k) {
+    const int64_t t = I * kSymTile + k * 64 + lane;
+    const float4 p = src[t];
+    xi[k] = p.x * pp.sig;
+    yi[k] = p.y * pp.sig;
+    zi[k] = p.z * pp.sig;
+    gi[k] = g[t];
+  }
+  const int64_t j = J * kSymTile + grp * 64 + lane;
+  if (wave == 0) {
+    const float4 s4 = src[j];
+    const float4 v = make_float4(s4.x * pp.sig, s4.y * pp.sig, s4.z * pp.sig, g[j]);
+    srcs[lane] = v;
+    srcs[lane + 64] = v;
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int round = 0; round < kSymRounds; ++round) {
+    const float4* const mine = srcs + lane + 64 - STEPS * (kSymSplit * round + wave);   // step s of this wave at -s
+    float u[STEPS][TPT];
+#pragma unroll
+    for (int step = 0; step < STEPS; ++step) {
+      const float4 q = mine[-step];
+#pragma unroll
+      for (int k = 0; k < TPT; ++k) {
+        const float r2 = pair_r2<KIND>(xi[k] - q.x, yi[k] - q.y, zi[k] - q.z, pp.per);
+        const float t = ((KIND & 1) == 0) ? r2 : __builtin_amdgcn_sqrtf(r2);
+        u[step][k] = pair_u<KIND>(t, pp.rho, pp.kappa);
+      }
+    }
+#pragma unroll 1
+    for (int w = 0; w < kSymSplit; ++w) {
+      if (wave == w) {
+        const bool first = round == 0 && w == 0;
+        float rs[TPT], cs = 0.0f;
+#pragma unroll
+        for (int k = 0; k < TPT; ++k) rs[k] = first ? 0.0f : hand[k][lane];
+        if (COLS && !first) cs = hand[TPT][lane];
+#pragma unroll
+        for (int step = 0; step < STEPS; ++step) {
+          const float gj = mine[-step].w;
+#pragma unroll
+          for (int k = 0; k < TPT; ++k) {
+            rs[k] = fmaf(u[step][k], gj, rs[k]);
+            if (COLS) cs = fmaf(u[step][k], gi[k], cs);
+          }
+          if (COLS) cs = wave_ror1(cs);
+        }
+        if (round + 1 < kSymRounds || w + 1 < kSymSplit) {
+#pragma unroll
+          for (int k = 0; k < TPT; ++k) hand[k][lane] = rs[k];
+          if (COLS) hand[TPT][lane] = cs;
+        } else {
+#pragma unroll
+          for (int k = 0; k < TPT; ++k) part[slot * npad + I * kSymTile + k * 64 + lane] = pp.amp * (double)rs[k];
+          if (COLS) part[I * npad + j] = pp.amp * (double)cs;
+        }
+      }
+      __syncthreads();
+    }
+  }
+}
+
 // part[s * npad + i]: slot s of node i (see above); nt = ceil(npad / (64 TPT)).
+// Workgroups below `whole` take a tile pair each; the four groups of every later
+// pair (rem pairs, the last of the order, fewer than two rows of it) take a
+// workgroup each.  Group 0's row sums go to slot J, group k's to the extra slot
+// nt + 3 (nt - 1 - J) + k - 1; the diagonal pairs clear the extra slots that no
+// group of their tile writes.
 template <int KIND, int TPT, int SPLIT>
 __global__ __launch_bounds__(64 * SPLIT) void k_otf_sym(const float4* __restrict__ src, const float* __restrict__ g,
-                                                        int64_t npad, PairParams pp, double* __restrict__ part) {
+                                                        int64_t npad, PairParams pp, SymRest rest,
+                                                        double* __restrict__ part) {
   __shared__ double rowsum[SPLIT][64 * TPT];
   __shared__ float4 srcs[SPLIT][128];
   int64_t I, J;
+  if constexpr (SPLIT == 4) {
+    static_assert(TPT == kSymTPT && SPLIT == kSymSplit, "one wave holds the tile's targets");
+    if (blockIdx.x >= rest.whole) {
+      const unsigned k = blockIdx.x - rest.whole;
+      const int grp = (int)(k & 3);
+      sym_decode(rest.whole + (k >> 2), &I, &J);
+      const int64_t nt = npad / kSymTile;
+      const int64_t slot = grp == 0 ? J : nt + 3 * (nt - 1 - J) + grp - 1;
+      float (*hand)[64] = reinterpret_cast<float (*)[64]>(&rowsum[0][0]);
+      if (I == J) {
+        sym_group<KIND, false>(src, g, npad, pp, part, I, J, grp, slot, srcs[0], hand);
+        if (grp == 0) sym_clear_rest(rest, npad, I, part);
+      } else {
+        sym_group<KIND, true>(src, g, npad, pp, part, I, J, grp, slot, srcs[0], hand);
+      }
+      return;
+    }
+  }
   sym_decode(blockIdx.x, &I, &J);
-  if (I == J)
+  if (I == J) {
     sym_tile<KIND, false, TPT, SPLIT>(src, g, npad, pp, part, I, J, rowsum, srcs);
-  else
+    if (SPLIT == 4) sym_clear_rest(rest, npad, I, part);
+  } else {
     sym_tile<KIND, true, TPT, SPLIT>(src, g, npad, pp, part, I, J, rowsum, srcs);
+  }
 }
 
 // ------------------------------------------------------------------ reductions

@@ -369,6 +369,22 @@ bool sym_small(int64_t npad) { return npad <= kSymSmallMaxNpad; }
 int64_t sym_tiles(int64_t npad) { return ceil_div(npad, sym_small(npad) ? 64 * kSymSmallTPT : kSymTile); }
 int64_t adj_tiles(int64_t npad) { return ceil_div(npad, kSymTile); }
 
+// The tile pairs beyond a whole number per compute unit are split into their
+// groups where that shortens the launch's end noticeably: up to kSymRestMax of
+// them (they are as many workgroups four times, each a third as long), in the
+// last two rows of the order (the extra slots), with at most 128 tiles (beyond,
+// the end is 2 % of the launch).
+#ifndef NFR_SYM_REST_MAX
+#define NFR_SYM_REST_MAX 192
+#endif
+constexpr int64_t kComputeUnits = 256, kSymRestMax = NFR_SYM_REST_MAX;
+SymRest sym_rest(int64_t npad) {
+  const int64_t nt = sym_tiles(npad), pairs = sym_pairs(nt), rem = pairs % kComputeUnits;
+  const bool split = !sym_small(npad) && nt <= 128 && rem <= kSymRestMax && rem < 2 * nt && rem < pairs;
+  const int64_t whole = split ? pairs - rem : pairs;
+  return SymRest{(unsigned)whole, whole == pairs ? 0 : (rem <= nt ? 1 : 2)};
+}
+
 // Up to this many padded nodes one state's pair sum is the one-sided
 // k_otf_small (kSmallRows targets per workgroup, one slot per node) instead of
 // the symmetric kernel.  RK4 step on the sphere, one-sided (one launch per
@@ -389,12 +405,15 @@ void launch_sym(const ProblemView& pv, const PairParams& pp, const float* g, dou
                        pv.n, pv.npad, pp, part, Rk4Stage{}, nullptr);
     return;
   }
-  const dim3 grid((unsigned)sym_pairs(sym_tiles(pv.npad)));
-  if (sym_small(pv.npad))
-    hipLaunchKernelGGL((k_otf_sym<K, kSymSmallTPT, kSymSmallSplit>), grid, dim3(64 * kSymSmallSplit), 0, s, pv.src, g,
-                       pv.npad, pp, part);
-  else
-    hipLaunchKernelGGL((k_otf_sym<K, kSymTPT, kSymSplit>), grid, dim3(kSymThreads), 0, s, pv.src, g, pv.npad, pp, part);
+  const int64_t pairs = sym_pairs(sym_tiles(pv.npad));
+  if (sym_small(pv.npad)) {
+    hipLaunchKernelGGL((k_otf_sym<K, kSymSmallTPT, kSymSmallSplit>), dim3((unsigned)pairs), dim3(64 * kSymSmallSplit), 0,
+                       s, pv.src, g, pv.npad, pp, SymRest{(unsigned)pairs, 0}, part);
+  } else {
+    const SymRest rest = sym_rest(pv.npad);
+    hipLaunchKernelGGL((k_otf_sym<K, kSymTPT, kSymSplit>), dim3((unsigned)(rest.whole + 4 * (pairs - rest.whole))),
+                       dim3(kSymThreads), 0, s, pv.src, g, pv.npad, pp, rest, part);
+  }
 }
 
 // B = 1 on the fly uses the symmetric kernel: one FP64 slot per tile and node,
@@ -413,7 +432,7 @@ bool sources_carry_q(int form) { return form == NFR_FORM_ONTHEFLY_FP32 || form =
 // Partial-sum slots per node of one pair launch; `otf` is the plan of the
 // multi-state on-the-fly FP32 sum (the only plan that reads the tune table).
 int nsplit_of(const ProblemView& pv, int B, int form, const OtfPlan& otf) {
-  if (use_sym(form, B, pv.npad)) return small_onesided(pv.npad) ? 1 : (int)sym_tiles(pv.npad);
+  if (use_sym(form, B, pv.npad)) return small_onesided(pv.npad) ? 1 : (int)sym_tiles(pv.npad) + 3 * sym_rest(pv.npad).rows;
   if (form == NFR_FORM_ONTHEFLY_FP32) return otf.nsplit;
   if (form == NFR_FORM_W_FP32) return plan_gemv(pv.n, pv.npad, B).nsplit;
   return mfma_nsplit(form);
