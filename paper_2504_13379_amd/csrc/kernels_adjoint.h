@@ -25,7 +25,7 @@ namespace nfr {
 // (kernels_core.h: tile pairs I <= J, the targets of tile I held kSymTPT per lane,
 // source groups of J split over the waves, sources rotated by DPP carrying
 // their column accumulators), here with four channels weighted by lambda.
-// Slots: part[(c * nt + s) * npad + i] for channel c, slot s (the row sums of
+// Slots: part[(c * nslots + s) * npad + i] for channel c, slot s (the row sums of
 // (I, J) go to slot J of the nodes of I, the column sums to slot I of the
 // nodes of J).  The coordinates are in the forward kernel's units (t the
 // excitatory argument); with rho = 1/m they are in units of the inhibitory
@@ -40,9 +40,9 @@ namespace nfr {
 constexpr int kAdjSplit = NFR_ADJ_SPLIT;
 constexpr int kAdjThreads = 64 * kAdjSplit;
 
-template <int KIND, bool COLS>
+template <int KIND, bool COLS, int UNROLL>
 __device__ inline void sym_adj_tile(const float4* __restrict__ src, const float* __restrict__ lam, int64_t npad,
-                                    int nt, const PairParams& pp, double* __restrict__ part, int64_t I, int64_t J,
+                                    int nslots, const PairParams& pp, double* __restrict__ part, int64_t I, int64_t J,
                                     double (*rowsum)[4][kSymTile], float4 (*srcs)[128]) {
   static_assert(kSymTile == 64 * kSymTPT, "one wave holds the tile's targets");
   const int lane = threadIdx.x & 63;
@@ -78,9 +78,11 @@ __device__ inline void sym_adj_tile(const float4* __restrict__ src, const float*
     for (int k = 0; k < kSymTPT; ++k)
 #pragma unroll
       for (int c = 0; c < 4; ++c) acc[k][c] = 0.0f;
-#pragma unroll 1
+    float4 next = srcs[wave][lane + 64];
+#pragma unroll UNROLL
     for (int step = 0; step < 64; ++step) {
-      const float4 q = srcs[wave][lane + 64 - step];
+      const float4 q = next;
+      next = srcs[wave][lane + 63 - step];
 #pragma unroll
       for (int k = 0; k < kSymTPT; ++k) {
         const float r2 = pair_r2<KIND>(xi[k] - q.x, yi[k] - q.y, zi[k] - q.z, pp.per);
@@ -113,7 +115,7 @@ __device__ inline void sym_adj_tile(const float4* __restrict__ src, const float*
       for (int c = 0; c < 4; ++c) racc[k][c] += (double)acc[k][c];
     if (COLS) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) part[((int64_t)c * nt + I) * npad + j] = (double)col[c];
+      for (int c = 0; c < 4; ++c) part[((int64_t)c * nslots + I) * npad + j] = (double)col[c];
     }
   }
   if (kAdjSplit > 1) {
@@ -130,7 +132,7 @@ __device__ inline void sym_adj_tile(const float4* __restrict__ src, const float*
         double sum = 0.0;
 #pragma unroll
         for (int w = 0; w < kAdjSplit; ++w) sum += rowsum[w][c][tt];
-        part[((int64_t)c * nt + J) * npad + t] = sum;
+        part[((int64_t)c * nslots + J) * npad + t] = sum;
       }
     }
   } else {
@@ -139,24 +141,123 @@ __device__ inline void sym_adj_tile(const float4* __restrict__ src, const float*
       const int64_t t = I * kSymTile + k * 64 + lane;
       if (t >= npad) continue;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) part[((int64_t)c * nt + J) * npad + t] = racc[k][c];
+      for (int c = 0; c < 4; ++c) part[((int64_t)c * nslots + J) * npad + t] = racc[k][c];
     }
   }
 }
 
-// One launch per reverse stage: nt (nt + 1) / 2 workgroups, nt = ceil(npad / kSymTile).
-template <int KIND>
+// One source group of a tile pair by the whole workgroup (compare sym_group): in
+// rounds of eight rotation steps the waves evaluate two steps each and put the
+// four channels' values into LDS, then wave c adds channel c for all eight.  The
+// sums are those of a wave alone, bit for bit, in about a third of its time.
+constexpr int kAdjRound = 8;
+template <int KIND, bool COLS>
+__device__ inline void sym_adj_group(const float4* __restrict__ src, const float* __restrict__ lam, int64_t npad,
+                                     int nslots, const PairParams& pp, double* __restrict__ part, int64_t I, int64_t J,
+                                     int grp, int64_t slot, float4* srcs, float (*val)[kAdjRound][kSymTPT][64]) {
+  // sym_adj_tile's coordinates are rounded before they meet in the differences
+#pragma clang fp contract(off)
+  static_assert(kAdjSplit == 4, "a wave per channel");
+  constexpr int TPT = kSymTPT, STEPS = kAdjRound / kAdjSplit;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float xi[TPT], yi[TPT], zi[TPT], li[TPT];
+#pragma unroll
+  for (int k = 0; k < TPT; ++k) {
+    const int64_t t = I * kSymTile + k * 64 + lane;
+    const float4 p = src[t];
+    xi[k] = p.x * pp.sig;
+    yi[k] = p.y * pp.sig;
+    zi[k] = p.z * pp.sig;
+    li[k] = lam[t];
+  }
+  const int64_t j = J * kSymTile + grp * 64 + lane;
+  if (wave == 0) {
+    const float4 s4 = src[j];
+    const float4 v = make_float4(s4.x * pp.sig, s4.y * pp.sig, s4.z * pp.sig, lam[j]);
+    srcs[lane] = v;
+    srcs[lane + 64] = v;
+  }
+  __syncthreads();
+  float rs[TPT], cs = 0.0f;       // of channel `wave`
+#pragma unroll
+  for (int k = 0; k < TPT; ++k) rs[k] = 0.0f;
+#pragma unroll 1
+  for (int s0 = 0; s0 < 64; s0 += kAdjRound) {
+#pragma unroll
+    for (int e = 0; e < STEPS; ++e) {
+      const int step = STEPS * wave + e;
+      const float4 q = srcs[lane + 64 - s0 - step];
+#pragma unroll
+      for (int k = 0; k < TPT; ++k) {
+        const float r2 = pair_r2<KIND>(xi[k] - q.x, yi[k] - q.y, zi[k] - q.z, pp.per);
+        const float t = ((KIND & 1) == 0) ? r2 : __builtin_amdgcn_sqrtf(r2);
+        const float e2 = sym_pow<KIND>() == 0 ? __builtin_amdgcn_exp2f(-(t * pp.rho)) : __builtin_amdgcn_exp2f(-t);
+        const float e1 = sym_pow<KIND>() == 0 ? __builtin_amdgcn_exp2f(-t) : ipow<sym_pow<KIND>()>(e2);
+        val[0][step][k][lane] = e1;
+        val[1][step][k][lane] = e2;
+        val[2][step][k][lane] = e1 * t;
+        val[3][step][k][lane] = e2 * t;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < kAdjRound; ++e) {
+      const float lj = srcs[lane + 64 - s0 - e].w;
+#pragma unroll
+      for (int k = 0; k < TPT; ++k) {
+        const float v = val[wave][e][k][lane];
+        rs[k] = fmaf(v, lj, rs[k]);
+        if (COLS) cs = fmaf(v, li[k], cs);
+      }
+      if (COLS) cs = wave_ror1(cs);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int k = 0; k < TPT; ++k)
+    part[((int64_t)wave * nslots + slot) * npad + I * kSymTile + k * 64 + lane] = (double)rs[k];
+  if (COLS) part[((int64_t)wave * nslots + I) * npad + j] = (double)cs;
+}
+
+// One launch per reverse stage.  Tile pairs below rest.whole take a workgroup
+// each, the groups of the later ones a workgroup each, with the slots of
+// k_otf_sym: nslots = nt + 3 rest.rows per channel, nt = npad / kSymTile.  UNROLL:
+// rotation steps per iteration, 1 as in k_otf_sym (N = 16384: 93 -> 76 us per
+// launch) or, where a few waves must hide their own latencies, more.
+template <int KIND, int UNROLL>
 __global__ __launch_bounds__(kAdjThreads) void k_sym_adjoint(const float4* __restrict__ src,
-                                                             const float* __restrict__ lam, int64_t npad, int nt,
-                                                             PairParams pp, double* __restrict__ part) {
+                                                             const float* __restrict__ lam, int64_t npad,
+                                                             PairParams pp, SymRest rest, double* __restrict__ part) {
   __shared__ double rowsum[kAdjSplit][4][kSymTile];
   __shared__ float4 srcs[kAdjSplit][128];
+  const int nt = (int)(npad / kSymTile), nslots = nt + 3 * rest.rows;
+  auto clear = [&](int64_t I) {
+    for (int c = 0; c < 4; ++c) sym_clear_rest(rest, npad, I, part + (int64_t)c * nslots * npad);
+  };
   int64_t I, J;
+  if (blockIdx.x >= rest.whole) {
+    const unsigned k = blockIdx.x - rest.whole;
+    const int grp = (int)(k & 3);
+    sym_decode(rest.whole + (k >> 2), &I, &J);
+    const int64_t slot = grp == 0 ? J : nt + 3 * (nt - 1 - J) + grp - 1;
+    auto val = reinterpret_cast<float (*)[kAdjRound][kSymTPT][64]>(&rowsum[0][0][0]);
+    static_assert(sizeof(rowsum) >= 4 * kAdjRound * kSymTPT * 64 * sizeof(float), "a round's values");
+    if (I == J) {
+      sym_adj_group<KIND, false>(src, lam, npad, nslots, pp, part, I, J, grp, slot, srcs[0], val);
+      if (grp == 0) clear(I);
+    } else {
+      sym_adj_group<KIND, true>(src, lam, npad, nslots, pp, part, I, J, grp, slot, srcs[0], val);
+    }
+    return;
+  }
   sym_decode(blockIdx.x, &I, &J);
-  if (I == J)
-    sym_adj_tile<KIND, false>(src, lam, npad, nt, pp, part, I, J, rowsum, srcs);
-  else
-    sym_adj_tile<KIND, true>(src, lam, npad, nt, pp, part, I, J, rowsum, srcs);
+  if (I == J) {
+    sym_adj_tile<KIND, false, UNROLL>(src, lam, npad, nslots, pp, part, I, J, rowsum, srcs);
+    clear(I);
+  } else {
+    sym_adj_tile<KIND, true, UNROLL>(src, lam, npad, nslots, pp, part, I, J, rowsum, srcs);
+  }
 }
 
 // Coefficients turning the raw sums into dw/dp terms:

@@ -466,9 +466,11 @@ __device__ inline void sym_tile(const float4* __restrict__ src, const float* __r
     float rs[kSymTPT];
 #pragma unroll
     for (int k = 0; k < kSymTPT; ++k) rs[k] = 0.0f;
+    float4 next = srcs[wave][lane + 64];   // a step ahead: few waves hide its latency on small problems
 #pragma unroll NFR_SYM_UNROLL
     for (int step = 0; step < 64; ++step) {
-      const float4 q = srcs[wave][lane + 64 - step];
+      const float4 q = next;
+      next = srcs[wave][lane + 63 - step];
 #pragma unroll
       for (int k = 0; k < kSymTPT; ++k) {
         const float r2 = pair_r2<KIND>(xi[k] - q.x, yi[k] - q.y, zi[k] - q.z, pp.per);

@@ -371,19 +371,30 @@ int64_t adj_tiles(int64_t npad) { return ceil_div(npad, kSymTile); }
 
 // The tile pairs beyond a whole number per compute unit are split into their
 // groups where that shortens the launch's end noticeably: up to kSymRestMax of
-// them (they are as many workgroups four times, each a third as long), in the
-// last two rows of the order (the extra slots), with at most 128 tiles (beyond,
-// the end is 2 % of the launch).
+// them (they are as many workgroups four times, each a third as long), with at
+// most 128 tiles (beyond, the end is 2 % of the launch).  The extra slots are
+// three for each of the last rows of the order that such a pair lies in.
+// `all` (the transpose kernel): every pair is split up to kSymAllMax (gradients
+// of 10 steps, N = 1544: 1.83 -> 1.73 ms; at 78 pairs 3 % slower than whole).
 #ifndef NFR_SYM_REST_MAX
 #define NFR_SYM_REST_MAX 192
 #endif
-constexpr int64_t kComputeUnits = 256, kSymRestMax = NFR_SYM_REST_MAX;
-SymRest sym_rest(int64_t npad) {
-  const int64_t nt = sym_tiles(npad), pairs = sym_pairs(nt), rem = pairs % kComputeUnits;
-  const bool split = !sym_small(npad) && nt <= 128 && rem <= kSymRestMax && rem < 2 * nt && rem < pairs;
-  const int64_t whole = split ? pairs - rem : pairs;
-  return SymRest{(unsigned)whole, whole == pairs ? 0 : (rem <= nt ? 1 : 2)};
+#ifndef NFR_SYM_ALL_MAX
+#define NFR_SYM_ALL_MAX 64
+#endif
+constexpr int64_t kComputeUnits = 256, kSymRestMax = NFR_SYM_REST_MAX, kSymAllMax = NFR_SYM_ALL_MAX;
+SymRest sym_rest_of(int64_t nt, bool all) {
+  const int64_t pairs = sym_pairs(nt);
+  int64_t rem = nt <= 128 ? pairs % kComputeUnits : 0;
+  if (rem > kSymRestMax || rem == pairs) rem = 0;
+  if (all && pairs <= kSymAllMax) rem = pairs;
+  SymRest r{(unsigned)(pairs - rem), 0};
+  for (int64_t left = rem; left > 0; left -= nt - r.rows, ++r.rows) {}
+  return r;
 }
+SymRest sym_rest(int64_t npad) { return sym_small(npad) ? SymRest{(unsigned)sym_pairs(sym_tiles(npad)), 0} : sym_rest_of(sym_tiles(npad), false); }
+SymRest adj_rest(int64_t npad) { return sym_rest_of(adj_tiles(npad), true); }
+int adj_slots(int64_t npad) { return (int)adj_tiles(npad) + 3 * adj_rest(npad).rows; }
 
 // Up to this many padded nodes one state's pair sum is the one-sided
 // k_otf_small (kSmallRows targets per workgroup, one slot per node) instead of
@@ -1356,7 +1367,7 @@ AdjWorkspace carve_adjoint(void* base, const ProblemView& pv, int64_t ckpt_every
     off += align256(bytes);
     return r;
   };
-  const int nsplit = (int)adj_tiles(pv.npad);
+  const int nsplit = adj_slots(pv.npad);
   const int64_t nblocks = adj_blocks(pv.n, nsplit);
   a.store = reinterpret_cast<double*>(take(size_t(ckpt_every) * 4 * pv.n * sizeof(double)));
   a.useg = reinterpret_cast<double*>(take(size_t(pv.n) * sizeof(double)));
@@ -1419,10 +1430,12 @@ int nfr_adjoint(nfr_problem* prob, const nfr_kernel* kernel, const nfr_firing* f
   const Firing fr = firing_of(*firing);
   const PairParams pp = pair_params_pow(*kernel, pv);
   const AdjCoef co = adj_coef(*kernel);
-  const int nt = (int)adj_tiles(pv.npad);
+  const int nslots = adj_slots(pv.npad);
+  const SymRest rest = adj_rest(pv.npad);
+  const bool few = sym_pairs(adj_tiles(pv.npad)) <= kComputeUnits;   // at most a wave per SIMD
   const int adj_code = kind_code(*kernel, pv) | (sym_pow_code(*kernel) << 2);
   const int64_t n = pv.n;
-  const int64_t nblocks = adj_blocks(n, nt);
+  const int64_t nblocks = adj_blocks(n, nslots);
   const size_t vbytes = size_t(n) * sizeof(double);
   const int form = NFR_FORM_ONTHEFLY_FP32;
 
@@ -1448,9 +1461,14 @@ int nfr_adjoint(nfr_problem* prob, const nfr_kernel* kernel, const nfr_firing* f
     for (int64_t l = len - 1; l >= 0; --l) {
       for (int stage = 4; stage >= 1; --stage) {
         if ((r = timing_mark(ctx))) return r;
-        const dim3 agrid((unsigned)sym_pairs(nt));
+        const dim3 agrid((unsigned)(rest.whole + 4 * (sym_pairs(adj_tiles(pv.npad)) - rest.whole)));
 #define NFR_ADJ_CASE(K) \
-  case K: hipLaunchKernelGGL(k_sym_adjoint<K>, agrid, dim3(kAdjThreads), 0, s, pv.src, a.lam32, pv.npad, nt, pp, a.apart); break;
+  case K:                                                                                                              \
+    if (few)                                                                                                           \
+      hipLaunchKernelGGL((k_sym_adjoint<K, 4>), agrid, dim3(kAdjThreads), 0, s, pv.src, a.lam32, pv.npad, pp, rest, a.apart); \
+    else                                                                                                               \
+      hipLaunchKernelGGL((k_sym_adjoint<K, 1>), agrid, dim3(kAdjThreads), 0, s, pv.src, a.lam32, pv.npad, pp, rest, a.apart); \
+    break;
         switch (adj_code) {
           NFR_ADJ_CASE(0) NFR_ADJ_CASE(1) NFR_ADJ_CASE(2) NFR_ADJ_CASE(3)
           NFR_ADJ_CASE(4) NFR_ADJ_CASE(5) NFR_ADJ_CASE(6) NFR_ADJ_CASE(7)
@@ -1461,7 +1479,7 @@ int nfr_adjoint(nfr_problem* prob, const nfr_kernel* kernel, const nfr_firing* f
 #undef NFR_ADJ_CASE
         NFR_HIP_LAUNCH();
         if ((r = timing_mark(ctx))) return r;
-        NFR_LAUNCH_SLOTS(k_adj_combine, nt, n, s, a.apart, nt, n, pv.npad,
+        NFR_LAUNCH_SLOTS(k_adj_combine, nslots, n, s, a.apart, nslots, n, pv.npad,
                            stage, dt, co, pv.q, fr, a.store + (l * 4 + stage - 1) * n, a.ubar, a.unbar, a.lam,
                            a.lam32, a.pblk);
         NFR_HIP_LAUNCH();
