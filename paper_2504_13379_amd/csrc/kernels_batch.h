@@ -2,9 +2,9 @@
 // and state counts) advanced together, one persistent pair-sum launch and one
 // combine launch per RK4 stage for the whole batch.
 //
-// Work items are (problem, target tile of kWG * batch_tpt(bs) targets, source
-// chunk, state block); they are sorted by decreasing cost on the host and a fixed grid of
-// workgroups walks them round-robin, so every stage is a single launch whose
+// Work items are (problem, target tile of kBatchTile targets, source chunk, state
+// block); they are sorted by decreasing cost on the host and a fixed grid of
+// workgroups walks them round by round, so every stage is a single launch whose
 // largest items start first.
 #pragma once
 
@@ -37,46 +37,48 @@ struct BatchItem {
   int sb;
 };
 
-// State block of a problem with B states (1, 4 or 16; see batch_tpt for the
-// targets per thread that go with it).
+// State block of a problem with B states (1, 4 or 16, the last on the matrix cores).
 __host__ __device__ constexpr int batch_bs(int B) { return B == 1 ? 1 : (B <= 4 ? 4 : 16); }
 
-// Targets per thread of a batch item with state block bs.  One kernel serves
-// every block size and takes the register allocation of the largest, so the
-// two targets per thread that the single-problem 16-state sum uses (201
-// registers) would cut the occupancy of every item; one target (148
-// registers) is faster over the uneven batch (1.39e13 against 1.30e13
-// pair-interactions/s).
-#ifndef NFR_BATCH_TPT16
-#define NFR_BATCH_TPT16 1
-#endif
-__host__ __device__ constexpr int batch_tpt(int bs) { return bs == 16 ? NFR_BATCH_TPT16 : otf_tpt(bs); }
+constexpr int kBatchTile = 256;     // targets of every item
+
+// LDS of one item: the vector form's, or the matrix-core form's tile of 16 states.
+struct BatchMfmaLds {
+  float4 src[kWG];
+  float g[16][kOtfGStride];
+};
+constexpr size_t kBatchLds = sizeof(BatchMfmaLds) > sizeof(OtfLds<4>) ? sizeof(BatchMfmaLds) : sizeof(OtfLds<4>);
 
 template <int KIND>
-__device__ inline void batch_item(const BatchProblemDev& P, const BatchItem& w, float4* s_src,
-                                  float (*s_g)[kOtfGStride]) {
-  if (P.bs == 1)
-    otf_tile<KIND, batch_tpt(1), 1>(P.src, P.g, P.npad, P.B, P.chunk, P.pp, P.part, w.tile, w.split, w.sb, s_src, s_g);
-  else if (P.bs == 4)
-    otf_tile<KIND, batch_tpt(4), 4>(P.src, P.g, P.npad, P.B, P.chunk, P.pp, P.part, w.tile, w.split, w.sb * 4, s_src,
-                                  s_g);
-  else
-    otf_tile<KIND, batch_tpt(16), 16>(P.src, P.g, P.npad, P.B, P.chunk, P.pp, P.part, w.tile, w.split, w.sb * 16,
-                                    s_src, s_g);
+__device__ inline void batch_item(const BatchProblemDev& P, const BatchItem& w, char* lds) {
+  static_assert(64 * otf_tpt(4) == kBatchTile && kWG == kBatchTile, "one tile size");
+  if (P.bs == 1) {
+    otf_tile<KIND, otf_tpt(1), 1>(P.src, P.g, P.npad, P.B, P.chunk, P.pp, P.part, w.tile, w.split, w.sb,
+                                  *reinterpret_cast<OtfLds<1>*>(lds));
+  } else if (P.bs == 4) {
+    otf_tile<KIND, otf_tpt(4), 4>(P.src, P.g, P.npad, P.B, P.chunk, P.pp, P.part, w.tile, w.split, w.sb * 4,
+                                  *reinterpret_cast<OtfLds<4>*>(lds));
+  } else {
+    BatchMfmaLds& m = *reinterpret_cast<BatchMfmaLds*>(lds);
+    otf_mfma_tile<KIND, 1>(P.src, P.g, P.npad, P.B, P.chunk, P.pp, P.part, w.tile, w.split, w.sb * 16, m.src, m.g);
+  }
 }
 
-__global__ __launch_bounds__(kWG) void k_batch_pairs(const BatchProblemDev* __restrict__ probs,
-                                                     const BatchItem* __restrict__ items, int nitems) {
-  __shared__ float4 s_src[kWG];
-  __shared__ float s_g[16][kOtfGStride];
-  for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
+__global__ __launch_bounds__(kWG, 4) void k_batch_pairs(const BatchProblemDev* __restrict__ probs,
+                                                        const BatchItem* __restrict__ items, int nitems) {
+  __shared__ __attribute__((aligned(16))) char lds[kBatchLds];
+  // rounds alternate in direction, so that the workgroup with a round's
+  // largest item takes the next round's smallest
+  for (int r0 = 0, r = 0; r0 < nitems; r0 += gridDim.x, ++r) {
+    const int it = r0 + (int)((r & 1) ? gridDim.x - 1 - blockIdx.x : blockIdx.x);
+    if (it >= nitems) continue;
     const BatchItem w = items[it];
     const BatchProblemDev& P = probs[w.p];
     switch (P.kind) {
-      case 0: batch_item<0>(P, w, s_src, s_g); break;
-      case 1: batch_item<1>(P, w, s_src, s_g); break;
-      case 2: batch_item<2>(P, w, s_src, s_g); break;
-      default: batch_item<3>(P, w, s_src, s_g); break;
+      case 0: batch_item<0>(P, w, lds); break;
+      case 1: batch_item<1>(P, w, lds); break;
+      case 2: batch_item<2>(P, w, lds); break;
+      default: batch_item<3>(P, w, lds); break;
     }
   }
 }

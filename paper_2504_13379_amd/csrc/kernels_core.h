@@ -146,31 +146,48 @@ __device__ __forceinline__ float pair_u(float t, float rho, float kappa) {
 
 // Partial pair sums over one source chunk:
 //   part[(split*B + b)*npad + i] = sum_{j in chunk(split)} w(|x_i - x_j|) g[b*npad + j]
-// Grid: x = target tiles of kWG*TPT targets (thread t owns tile + t + kWG*k),
+// Grid: x = target tiles of 64*TPT targets (lane l owns tile + l + 64*k in every wave),
 //       y = source chunks of `chunk` nodes (a multiple of kWG),
 //       z = state blocks of BS states.
-// Sources are staged kWG at a time in LDS as scaled float4 coordinates plus
-// their g values and read back as broadcasts.  Each thread sums one LDS tile
-// of kWG sources in FP32 (the normalised kernel u, see PairParams), then folds
-// the tile sum into FP64 accumulators: amp * sum.
-// Targets per thread for a block of BS states (TPT x BS accumulators per thread).
+// The four waves of a workgroup share the targets and take the chunk's source
+// tiles of kWG nodes in turn, each on its own (no barrier until the end): 64
+// sources at a time go to LDS as scaled coordinates plus their g values and are
+// read back as broadcasts, the next 64 on their way in registers meanwhile.  A
+// wave sums one tile of kWG sources in FP32 (the normalised kernel u, see
+// PairParams), then folds the tile sum into FP64 accumulators: amp * sum; the
+// waves' accumulators are added in wave order through LDS.  (With four waves of
+// targets per workgroup an item of the uneven batch held 1024 targets, and a
+// stage lasted as long as the slowest of them.)
+// Targets per lane for a block of BS states (TPT x BS accumulators per lane); fewer
+// where a problem gives too few workgroups.
 __host__ __device__ constexpr int otf_tpt(int bs) { return bs <= 4 ? 4 : 2; }
 
-constexpr int kOtfGStride = kWG + 4;     // floats per LDS row of g: the matrix-core form reads 16 rows at once
+constexpr int kOtfGStride = kWG + 4;     // floats per LDS row of g in the matrix-core form, which reads 16 rows at once
+// Sources per iteration (b states): N = 20011, 2 states 3.31 ms per 20 applications
+// with 2 against 3.38 with 4, 7 states 4.42 with 4 against 4.74 with 2.
+__host__ __device__ constexpr int otf_unroll(int bs) { return bs >= 8 ? 4 : 2; }
+
+// LDS of otf_tile.
+template <int BS>
+struct OtfLds {
+  float4 src[4][64];          // x, y, z, g of the first state
+  float g[4][64][BS];
+  double red[4][256];
+};
 
 template <int KIND, int TPT, int BS>
 __device__ inline void otf_tile(const float4* __restrict__ src, const float* __restrict__ g, int64_t npad, int B,
                                 int64_t chunk, const PairParams& pp, double* __restrict__ part, int64_t tile,
-                                int split, int b0, float4* s_src, float (*s_g)[kOtfGStride]) {
+                                int split, int b0, OtfLds<BS>& lds) {
   const int tid = threadIdx.x;
-  const int64_t tbase = tile * (kWG * TPT);
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t tbase = tile * (64 * TPT);
 
   float xi[TPT], yi[TPT], zi[TPT];
 #pragma unroll
   for (int k = 0; k < TPT; ++k) {
-    int64_t t = tbase + tid + (int64_t)kWG * k;
-    if (t >= npad) t = npad - 1;
-    const float4 p = src[t];
+    const float4 p = src[tbase + lane + 64 * k];     // npad is a multiple of 64 TPT
     xi[k] = p.x * pp.sig;
     yi[k] = p.y * pp.sig;
     zi[k] = p.z * pp.sig;
@@ -187,37 +204,51 @@ __device__ inline void otf_tile(const float4* __restrict__ src, const float* __r
   const float rho = pp.rho;
   const float kappa = pp.kappa;
 
-  for (int64_t j0 = j_begin; j0 < j_end; j0 += kWG) {
-    {
-      const float4 s = src[j0 + tid];
-      s_src[tid] = make_float4(s.x * pp.sig, s.y * pp.sig, s.z * pp.sig, 0.0f);
+  float4 sn;
+  float gn[BS];
+  auto fetch = [&](int64_t j) {
+    sn = src[j + lane];
 #pragma unroll
-      for (int b = 0; b < BS; ++b)
-        s_g[b][tid] = (b0 + b < B) ? g[(int64_t)(b0 + b) * npad + j0 + tid] : 0.0f;
-    }
-    __syncthreads();
+    for (int b = 0; b < BS; ++b) gn[b] = (b0 + b < B) ? g[(int64_t)(b0 + b) * npad + j + lane] : 0.0f;
+  };
+  int64_t j0 = j_begin + (int64_t)wave * kWG;
+  if (j0 < j_end) fetch(j0);
+  for (; j0 < j_end; j0 += 4 * kWG) {
     float a[TPT][BS];
 #pragma unroll
     for (int k = 0; k < TPT; ++k)
 #pragma unroll
       for (int b = 0; b < BS; ++b) a[k][b] = 0.0f;
-
-#pragma unroll 4
-    for (int jj = 0; jj < kWG; ++jj) {
-      const float4 s = s_src[jj];
-      float gv[BS];
+#pragma unroll 1
+    for (int sl = 0; sl < kWG / 64; ++sl) {
+      __builtin_amdgcn_wave_barrier();   // the previous slice's reads come first
+      lds.src[wave][lane] = make_float4(sn.x * pp.sig, sn.y * pp.sig, sn.z * pp.sig, gn[0]);
+      if (BS > 1) {
 #pragma unroll
-      for (int b = 0; b < BS; ++b) gv[b] = s_g[b][jj];
+        for (int b = 0; b < BS; ++b) lds.g[wave][lane][b] = gn[b];
+      }
+      __builtin_amdgcn_wave_barrier();
+      const int64_t jn = sl + 1 < kWG / 64 ? j0 + 64 * (sl + 1) : j0 + 4 * kWG;
+      if (jn < j_end) fetch(jn);
+#pragma unroll otf_unroll(BS)
+      for (int jj = 0; jj < 64; ++jj) {
+        const float4 s = lds.src[wave][jj];
+        float gv[BS];
+        gv[0] = s.w;
+        if (BS > 1) {
 #pragma unroll
-      for (int k = 0; k < TPT; ++k) {
-        const float r2 = pair_r2<KIND>(xi[k] - s.x, yi[k] - s.y, zi[k] - s.z, pp.per);
-        const float t = ((KIND & 1) == 0) ? r2 : __builtin_amdgcn_sqrtf(r2);
-        const float u = pair_u<KIND>(t, rho, kappa);
+          for (int b = 0; b < BS; ++b) gv[b] = lds.g[wave][jj][b];
+        }
 #pragma unroll
-        for (int b = 0; b < BS; ++b) a[k][b] = fmaf(u, gv[b], a[k][b]);
+        for (int k = 0; k < TPT; ++k) {
+          const float r2 = pair_r2<KIND>(xi[k] - s.x, yi[k] - s.y, zi[k] - s.z, pp.per);
+          const float t = ((KIND & 1) == 0) ? r2 : __builtin_amdgcn_sqrtf(r2);
+          const float u = pair_u<KIND>(t, rho, kappa);
+#pragma unroll
+          for (int b = 0; b < BS; ++b) a[k][b] = fmaf(u, gv[b], a[k][b]);
+        }
       }
     }
-    __syncthreads();
 #pragma unroll
     for (int k = 0; k < TPT; ++k)
 #pragma unroll
@@ -225,13 +256,17 @@ __device__ inline void otf_tile(const float4* __restrict__ src, const float* __r
   }
 
 #pragma unroll
-  for (int k = 0; k < TPT; ++k) {
-    const int64_t t = tbase + tid + (int64_t)kWG * k;
-    if (t >= npad) continue;
+  for (int b = 0; b < BS; ++b) {
+    if (b0 + b >= B) break;
+    __syncthreads();
 #pragma unroll
-    for (int b = 0; b < BS; ++b)
-      if (b0 + b < B) part[((int64_t)split * B + b0 + b) * npad + t] = acc[k][b];
+    for (int k = 0; k < TPT; ++k) lds.red[wave][k * 64 + lane] = acc[k][b];
+    __syncthreads();
+    if (tid < 64 * TPT)
+      part[((int64_t)split * B + b0 + b) * npad + tbase + tid] =
+          ((lds.red[0][tid] + lds.red[1][tid]) + lds.red[2][tid]) + lds.red[3][tid];
   }
+  __syncthreads();                       // the LDS is free for the next item
 }
 
 // The same sums for blocks of BS = 16 NB states with the products on the FP32
@@ -334,9 +369,8 @@ template <int KIND, int TPT, int BS>
 __global__ __launch_bounds__(kWG) void k_otf_pair_sum(const float4* __restrict__ src, const float* __restrict__ g,
                                                       int64_t npad, int B, int64_t chunk, PairParams pp,
                                                       double* __restrict__ part) {
-  __shared__ float4 s_src[kWG];
-  __shared__ float s_g[BS][kOtfGStride];
-  otf_tile<KIND, TPT, BS>(src, g, npad, B, chunk, pp, part, blockIdx.x, blockIdx.y, blockIdx.z * BS, s_src, s_g);
+  __shared__ OtfLds<BS> lds;
+  otf_tile<KIND, TPT, BS>(src, g, npad, B, chunk, pp, part, blockIdx.x, blockIdx.y, blockIdx.z * BS, lds);
 }
 
 // ------------------------------------------------------------------ symmetric on-the-fly pair sum

@@ -253,7 +253,7 @@ constexpr int64_t kGraphMaxSteps = 64;  // RK4 steps per captured graph of nfr_i
 constexpr int64_t kBatchGraphMaxSteps = 16;  // RK4 steps per captured graph of nfr_batch_integrate
 
 struct OtfPlan {
-  int bs = 1, nsb = 1;
+  int bs = 1, nsb = 1, tpt = 1;
   int64_t tiles = 0, chunk = 0;
   int nsplit = 1;
 };
@@ -267,7 +267,6 @@ int otf_bs(int B) {
   if (B <= 8) return B == 1 ? 1 : (B == 2 ? 2 : (B <= 4 ? 4 : 8));
   return 16 * (int)ceil_div(ceil_div(B, 16), ceil_div(B, 64));
 }
-int64_t otf_tile_targets(int bs) { return (int64_t)kWG * (bs > 8 ? 1 : otf_tpt(bs)); }
 
 // Tuned workgroup targets of the multi-state on-the-fly pair sum (its one
 // free launch parameter: how many source chunks the work is cut into), keyed
@@ -312,15 +311,22 @@ OtfPlan plan_otf_target(int64_t npad, int B, int64_t target) {
   OtfPlan p;
   p.bs = otf_bs(B);
   p.nsb = (int)ceil_div(B, p.bs);
-  p.tiles = ceil_div(npad, otf_tile_targets(p.bs));
+  const bool vec = p.bs <= 8;
+  if (vec) {
+    // the waves of a workgroup share its targets and split its sources, four
+    // tiles of kWG at least; fewer targets per lane while that leaves compute
+    // units without a second workgroup
+    p.tpt = otf_tpt(p.bs);
+    while (p.tpt > 1 && p.bs > 1 && npad / (64 * p.tpt) * ceil_div(npad, 4 * kWG) * p.nsb < 512) p.tpt /= 2;
+  }
+  p.tiles = npad / (vec ? 64 * p.tpt : kWG);
+  const int64_t grain = vec ? 4 * kWG : kWG;
   int64_t want = ceil_div(2 * target, p.tiles * p.nsb);
   const int64_t slot = (int64_t)B * npad * 8, base = otf_base_split(npad, B, target);
   const int64_t room = ((int64_t)NFR_APPLY_NOALLOC_MAX_BYTES - 512 - npad * B * 4) / slot;
   if (base <= room && want > room) want = std::max(base, room);
-  const int64_t max_split = npad / kWG;
   if (want < 1) want = 1;
-  if (want > max_split) want = max_split;
-  p.chunk = round_up(ceil_div(npad, want), kWG);
+  p.chunk = round_up(ceil_div(npad, want), grain);
   p.nsplit = (int)ceil_div(npad, p.chunk);
   return p;
 }
@@ -511,14 +517,13 @@ template <int KIND>
 void launch_otf_kind(const ProblemView& pv, const PairParams& pp, int B, const float* g, double* part,
                      const OtfPlan& pl, hipStream_t s) {
   dim3 grid((unsigned)pl.tiles, (unsigned)pl.nsplit, (unsigned)pl.nsb);
-  if (pl.bs == 1)
-    hipLaunchKernelGGL((k_otf_pair_sum<KIND, otf_tpt(1), 1>), grid, dim3(kWG), 0, s, pv.src, g, pv.npad, B, pl.chunk, pp, part);
-  else if (pl.bs == 2)
-    hipLaunchKernelGGL((k_otf_pair_sum<KIND, otf_tpt(2), 2>), grid, dim3(kWG), 0, s, pv.src, g, pv.npad, B, pl.chunk, pp, part);
-  else if (pl.bs == 4)
-    hipLaunchKernelGGL((k_otf_pair_sum<KIND, otf_tpt(4), 4>), grid, dim3(kWG), 0, s, pv.src, g, pv.npad, B, pl.chunk, pp, part);
-  else if (pl.bs == 8)
-    hipLaunchKernelGGL((k_otf_pair_sum<KIND, otf_tpt(8), 8>), grid, dim3(kWG), 0, s, pv.src, g, pv.npad, B, pl.chunk, pp, part);
+#define NFR_OTF_CASE(BS, TPT) \
+  if (pl.bs == BS && pl.tpt == TPT) \
+    hipLaunchKernelGGL((k_otf_pair_sum<KIND, TPT, BS>), grid, dim3(kWG), 0, s, pv.src, g, pv.npad, B, pl.chunk, pp, part);
+  NFR_OTF_CASE(1, 4) else NFR_OTF_CASE(2, 4) else NFR_OTF_CASE(2, 2) else NFR_OTF_CASE(2, 1)
+  else NFR_OTF_CASE(4, 4) else NFR_OTF_CASE(4, 2) else NFR_OTF_CASE(4, 1)
+  else NFR_OTF_CASE(8, 2) else NFR_OTF_CASE(8, 1)
+#undef NFR_OTF_CASE
   else if (pl.bs == 16)
     hipLaunchKernelGGL((k_otf_mfma_sum<KIND, 1>), grid, dim3(kWG), 0, s, pv.src, g, pv.npad, B, pl.chunk, pp, part);
   else if (pl.bs == 32)
@@ -1574,8 +1579,11 @@ struct nfr_batch {
   std::vector<nfr_kernel> kernels;
   std::vector<nfr_firing> firings;
   std::vector<int> B;
+  // sixteen workgroups per compute unit, four of them resident: the rest start as
+  // others end (24 problems of 1000 to 20000 nodes: 792 us per stage, 901 with
+  // four of the former items)
   int64_t chunk = 2048;
-  int wgs_per_cu = 4;
+  int wgs_per_cu = 16;
   std::vector<BatchProblemDev> table;
   std::vector<BatchItem> items;
 };
@@ -1583,7 +1591,7 @@ struct nfr_batch {
 namespace {
 
 constexpr int64_t kBatchChunks[] = {1024, 2048, 4096, 8192};
-constexpr int kBatchWgs[] = {2, 4, 8};
+constexpr int kBatchWgs[] = {4, 8, 16};
 constexpr int64_t kBatchMinChunk = 1024;
 
 struct BatchLayout {
@@ -1594,8 +1602,7 @@ struct BatchLayout {
 
 int64_t batch_items_for(const nfr_problem* p, int B, int64_t chunk) {
   const int64_t npad = p->view.npad;
-  const int bs = batch_bs(B);
-  return ceil_div(npad, (int64_t)kWG * batch_tpt(bs)) * ceil_div(npad, chunk) * ceil_div(B, bs);
+  return npad / kBatchTile * ceil_div(npad, chunk) * ceil_div(B, batch_bs(B));
 }
 
 BatchLayout batch_layout(const nfr_batch* b) {
@@ -1655,18 +1662,17 @@ void batch_build(nfr_batch* b, const BatchLayout& L, char* ws, double* const* u_
     d.gel_off = goff;
     eoff += pv.n * Bp;
     goff += pv.npad * Bp;
-    const int tpt = batch_tpt(d.bs);
-    const int64_t tiles = ceil_div(pv.npad, (int64_t)kWG * tpt);
+    const int64_t tiles = pv.npad / kBatchTile;
     const int sbs = (int)ceil_div(Bp, d.bs);
     for (int64_t t = 0; t < tiles; ++t)
       for (int sp = 0; sp < d.nsplit; ++sp)
         for (int sb = 0; sb < sbs; ++sb) {
-          const double tg = (double)std::min<int64_t>(kWG * tpt, pv.npad - t * kWG * tpt);
           const double sc = (double)std::min<int64_t>(b->chunk, pv.npad - sp * b->chunk);
           const double st = (double)std::min(d.bs, Bp - sb * d.bs);
-          const double per_pair = ((d.kind & 1) ? 1.3 : 1.0) + ((d.kind & 2) ? 0.2 : 0.0) + 0.25 * (st - 1.0);
+          // relative to one state: a multiply-add per further state, or the matrix cores' time for 16
+          const double per_pair = ((d.kind & 1) ? 1.3 : 1.0) + ((d.kind & 2) ? 0.2 : 0.0) + (d.bs == 16 ? 0.6 : 0.07 * (st - 1.0));
           b->items.push_back(BatchItem{p, (int)t, sp, sb});
-          cost.push_back(tg * sc * per_pair);
+          cost.push_back(sc * per_pair);
         }
   }
   std::vector<size_t> order(b->items.size());
