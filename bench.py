@@ -241,13 +241,14 @@ def ensemble_roofline(nm, npad, kind, kernel, avg_s, max_r2, far_frac=0.0):
                 "frac": flops / avg_s / MFMA_F32_PEAK, "traffic": measured_traffic(kname), "kernel": kname,
                 "alu_frac": float(npad) ** 2 * eval_slots(kind, m) / avg_s / VALU_LANES_PER_S}
     if nm == "otf_fp32":
-        # one-sided multi-state pair sum: per target-source pair one evaluation of u per block
-        # of 16 states (no integer-ratio shortcut in this kernel) + 1 FMA per state
-        kname = "k_otf_pair_sum<%d,2,16>" % kind
-        slots = float(npad) ** 2 * (-(-64 // 16) * eval_slots(kind, 0) + 64)
-        return {"bound": "alu", "achieved": slots / avg_s / 1e12, "peak": VALU_LANES_PER_S / 1e12,
-                "unit": "Tslot/s", "frac": slots / avg_s / VALU_LANES_PER_S, "traffic": measured_traffic(kname),
-                "kernel": kname}
+        # one-sided multi-state pair sum: per target-source pair one evaluation of u (no
+        # integer-ratio shortcut in this kernel) on the vector units and 64 products on the
+        # FP32 matrix cores, one per entry
+        kname = "k_otf_mfma_sum<%d,4>" % kind
+        flops = 2.0 * float(npad) ** 2 * 64
+        return {"bound": "mfma", "achieved": flops / avg_s / 1e12, "peak": MFMA_F32_PEAK / 1e12, "unit": "TFLOP/s",
+                "frac": flops / avg_s / MFMA_F32_PEAK, "traffic": measured_traffic(kname), "kernel": kname,
+                "alu_frac": float(npad) ** 2 * eval_slots(kind, 0) / avg_s / VALU_LANES_PER_S}
     # fused on-the-fly split forms: every W entry evaluated once per launch on the vector
     # units (t of the norm expansion on the FP32 matrix cores); the BF16 matrix cores do
     # 3 products x 2 flop x 64 states per entry.  The bound is the larger of the vector
@@ -521,12 +522,12 @@ def batch_leg(P, torch, args):
     pair_ints = sum(4.0 * steps * float(w.n) ** 2 * w.b for w in ws_list)
     # algorithmic slots of the pair kernel per stage: per target-source pair and state block
     # one evaluation of u (eval_slots: 16 for the Gaussian), plus 1 FMA per state; blocks of
-    # 1, 4 or 16 states
+    # 1, 4 or 16 states, the last with their products on the FP32 matrix cores
     slots = 0.0
     for w in ws_list:
         npad = -(-w.n // 256) * 256
         bs = 1 if w.b == 1 else (4 if w.b <= 4 else 16)
-        slots += float(npad) ** 2 * (-(-w.b // bs) * eval_slots(0, 0) + w.b)
+        slots += float(npad) ** 2 * (-(-w.b // bs) * eval_slots(0, 0) + (w.b if bs < 16 else 0))
     slots *= 4.0 * steps
     chunk, wgs = batch.config
     return {"workload": "48 problems, N log-uniform [1000, 40000], sphere/torus/ellipsoid/bumpy, Gauss Mexican hat, "

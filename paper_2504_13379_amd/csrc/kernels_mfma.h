@@ -118,7 +118,7 @@ __device__ inline int w_scale_exp(const double* __restrict__ qmax, double amp) {
 // of consecutive memory per group.  (With one row per workgroup every thread
 // loaded 32 strided doubles for its 8 entries, and the exponentials took the
 // library's general path after an FP64 division: 7.35 ms at N = 32768, now
-// 2.6, of which writing takes about 0.8.)
+// 2.07, of which writing takes about 0.8.)
 // Grid: x = row groups / kWBuildGroups, y = 16-column blocks / 4.
 constexpr int kWBuildGroups = 4;
 template <typename T, int KIND>
