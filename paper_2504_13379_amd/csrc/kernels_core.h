@@ -461,11 +461,11 @@ __device__ __forceinline__ void put_sources(float4* srcs, int lane, float4 v) {
 // the scheduler spreads them and loses that (N = 65536, Gaussian: 618 us per
 // launch with 1, 747 with 2, 750 with 4; exponential 606 / 736 / 690; forcing an
 // exponential every five instructions 15 % slower than 4).
-#ifndef NFR_SYM_UNROLL
-#define NFR_SYM_UNROLL 1
-#endif
+// Where a compute unit has at most two workgroups, their few waves hide less of
+// their own latency and four steps are better (N = 6914: 22.8 against 23.2 us per
+// stage).
 
-template <int KIND, bool COLS, int TPT, int SPLIT>
+template <int KIND, bool COLS, int TPT, int SPLIT, int UNROLL>
 __device__ inline void sym_tile(const float4* __restrict__ src, const float* __restrict__ g, int64_t npad,
                                 const PairParams& pp, double* __restrict__ part, int64_t I, int64_t J,
                                 double (*rowsum)[64 * TPT], float4 (*srcs)[128]) {
@@ -501,7 +501,7 @@ __device__ inline void sym_tile(const float4* __restrict__ src, const float* __r
 #pragma unroll
     for (int k = 0; k < kSymTPT; ++k) rs[k] = 0.0f;
     float4 next = srcs[wave][lane + 64];   // a step ahead: few waves hide its latency on small problems
-#pragma unroll NFR_SYM_UNROLL
+#pragma unroll UNROLL
     for (int step = 0; step < 64; ++step) {
       const float4 q = next;
       next = srcs[wave][lane + 63 - step];
@@ -647,7 +647,7 @@ __device__ inline void sym_group(const float4* __restrict__ src, const float* __
 // workgroup each.  Group 0's row sums go to slot J, group k's to the extra slot
 // nt + 3 (nt - 1 - J) + k - 1; the diagonal pairs clear the extra slots that no
 // group of their tile writes.
-template <int KIND, int TPT, int SPLIT>
+template <int KIND, int TPT, int SPLIT, int UNROLL>
 __global__ __launch_bounds__(64 * SPLIT) void k_otf_sym(const float4* __restrict__ src, const float* __restrict__ g,
                                                         int64_t npad, PairParams pp, SymRest rest,
                                                         double* __restrict__ part) {
@@ -674,10 +674,10 @@ __global__ __launch_bounds__(64 * SPLIT) void k_otf_sym(const float4* __restrict
   }
   sym_decode(blockIdx.x, &I, &J);
   if (I == J) {
-    sym_tile<KIND, false, TPT, SPLIT>(src, g, npad, pp, part, I, J, rowsum, srcs);
+    sym_tile<KIND, false, TPT, SPLIT, UNROLL>(src, g, npad, pp, part, I, J, rowsum, srcs);
     if (SPLIT == 4) sym_clear_rest(rest, npad, I, part);
   } else {
-    sym_tile<KIND, true, TPT, SPLIT>(src, g, npad, pp, part, I, J, rowsum, srcs);
+    sym_tile<KIND, true, TPT, SPLIT, UNROLL>(src, g, npad, pp, part, I, J, rowsum, srcs);
   }
 }
 

@@ -383,7 +383,7 @@ int64_t adj_tiles(int64_t npad) { return ceil_div(npad, kSymTile); }
 // `all` (the transpose kernel): every pair is split up to kSymAllMax (gradients
 // of 10 steps, N = 1544: 1.83 -> 1.73 ms; at 78 pairs 3 % slower than whole).
 #ifndef NFR_SYM_REST_MAX
-#define NFR_SYM_REST_MAX 192
+#define NFR_SYM_REST_MAX 128
 #endif
 #ifndef NFR_SYM_ALL_MAX
 #define NFR_SYM_ALL_MAX 64
@@ -424,12 +424,17 @@ void launch_sym(const ProblemView& pv, const PairParams& pp, const float* g, dou
   }
   const int64_t pairs = sym_pairs(sym_tiles(pv.npad));
   if (sym_small(pv.npad)) {
-    hipLaunchKernelGGL((k_otf_sym<K, kSymSmallTPT, kSymSmallSplit>), dim3((unsigned)pairs), dim3(64 * kSymSmallSplit), 0,
+    hipLaunchKernelGGL((k_otf_sym<K, kSymSmallTPT, kSymSmallSplit, 1>), dim3((unsigned)pairs), dim3(64 * kSymSmallSplit), 0,
                        s, pv.src, g, pv.npad, pp, SymRest{(unsigned)pairs, 0}, part);
   } else {
     const SymRest rest = sym_rest(pv.npad);
-    hipLaunchKernelGGL((k_otf_sym<K, kSymTPT, kSymSplit>), dim3((unsigned)(rest.whole + 4 * (pairs - rest.whole))),
-                       dim3(kSymThreads), 0, s, pv.src, g, pv.npad, pp, rest, part);
+    const dim3 grid((unsigned)(rest.whole + 4 * (pairs - rest.whole)));
+    if (pairs <= 2 * kComputeUnits)
+      hipLaunchKernelGGL((k_otf_sym<K, kSymTPT, kSymSplit, 4>), grid, dim3(kSymThreads), 0, s, pv.src, g, pv.npad, pp,
+                         rest, part);
+    else
+      hipLaunchKernelGGL((k_otf_sym<K, kSymTPT, kSymSplit, 1>), grid, dim3(kSymThreads), 0, s, pv.src, g, pv.npad, pp,
+                         rest, part);
   }
 }
 
