@@ -53,11 +53,11 @@ __global__ __launch_bounds__(kWG) void k_quad_centroids(const double* __restrict
 // ------------------------------------------------------------------ k nearest nodes
 
 // Nodes are binned into a uniform grid of cubic cells; a centroid's search
-// visits the cells in Chebyshev rings r = 0, 1, 2, ... around its own cell and
-// stops once its k-th key is below the squared distance from the centroid to
-// the boundary of the rings visited (every node outside lies beyond it; a
-// relative margin of 1e-12 covers the rounding of the binning and of that
-// bound).  The result is the exact k smallest (squared distance, index), the
+// takes the cells within r = 1, 2, ... of its own, all at once by selection
+// (quad_knn_select) or ring by ring (quad_knn_scan), and stops once its k-th
+// key is below the squared distance from the centroid to the boundary of the
+// cells visited (every node outside lies beyond it; a relative margin of 1e-12
+// covers the rounding of the binning and of that bound).  The result is the exact k smallest (squared distance, index), the
 // same as a full scan.
 
 struct QuadGrid {
