@@ -837,11 +837,13 @@ __global__ __launch_bounds__(kWG) void k_scan_apply(const int* __restrict__ cnt,
   if (i < n) off[i] = bsum[blockIdx.x] + s[threadIdx.x] - v;
 }
 
-// q_i = sum of node i's entries in a fixed order of their numbers, one wave per
-// node: up to kSumHeld entries are put in increasing order through LDS by their
-// rank among the others and added by a fixed tree; longer lists (never a mesh
-// of bounded valence) in increasing order, one after the other.  A thread per
-// node sorting its list in memory took 490 us at N = 65538, a wave 58.
+// q_i = sum of node i's entries in increasing order of their numbers, one after
+// the other from 0, one wave per node: up to kSumHeld entries are put in that
+// order through LDS by their rank among the others (every lane then adds the
+// same broadcasts); longer lists (never a mesh of bounded valence) are searched
+// for the next entry each time.  A thread per
+// node sorting its list in memory took 490 us at N = 65538, a wave 66 (60 with its
+// lanes adding strided parts, in another order).
 constexpr int kSumHeld = 256;
 __global__ __launch_bounds__(kWG) void k_quad_sum(const int64_t* __restrict__ off, const int* __restrict__ cnt,
                                                   int64_t n, const int* __restrict__ list,
@@ -868,8 +870,8 @@ __global__ __launch_bounds__(kWG) void k_quad_sum(const int64_t* __restrict__ of
       if (64 * c + lane < len) s_val[wave][r] = v[64 * c + lane];
     }
     __builtin_amdgcn_wave_barrier();
-    for (int c = lane; c < len; c += 64) acc += s_val[wave][c];
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+#pragma unroll 8
+    for (int c = 0; c < len; ++c) acc += s_val[wave][c];
   } else {
     int last = -1;
     for (int a = 0; a < len; ++a) {
