@@ -1081,12 +1081,14 @@ __host__ inline WeightEval weight_eval(const KernelF64& k) {
   return w;
 }
 
-// KIND: kernel kind, + 2 for a periodic problem.  Ae: the amplitude A_e, NaN
-// for a row with a coordinate that is not finite (row_amp); a column with a NaN
-// carries it in its weight (the exponentials drop NaN arguments).
+// w(|dx, dy, dz|) q, 0 (not -0) for q = 0 and at an infinite distance.  KIND:
+// kernel kind, + 2 for a periodic problem.  The exponentials drop NaN arguments,
+// so the builds ask wq_is_nan where a coordinate of the wave's rows or columns is
+// not finite (a select in every entry costs k_mfma_w_build one of four waves per
+// SIMD: 28 % slower).
 template <int KIND>
-__device__ __forceinline__ double kernel_w64(const KernelF64& k, const WeightEval& w, double Ae, double dx, double dy,
-                                             double dz) {
+__device__ __forceinline__ double kernel_wq64(const KernelF64& k, const WeightEval& w, double q, double dx, double dy,
+                                              double dz) {
   if (KIND & 2) {
     dx = fabs(dx);
     dx = fmin(dx, k.period - dx);
@@ -1095,15 +1097,16 @@ __device__ __forceinline__ double kernel_w64(const KernelF64& k, const WeightEva
   }
   const double r2 = dx * dx + dy * dy + dz * dz;
   const double d = (KIND & 1) ? sqrt(r2) : r2;
-  return Ae * exp2_64(-(d * w.ce)) - k.Ai * exp2_64(-(d * w.ci));
+  return fma(k.Ae * exp2_64(-(d * w.ce)) - k.Ai * exp2_64(-(d * w.ci)), q, 0.0);
 }
 
-__device__ __forceinline__ double row_amp(double Ae, double x, double y, double z) {
-  return Ae + ((x - x) + (y - y) + (z - z));
+// Whether the entry is NaN: its distance is, and q is not 0.
+__device__ __forceinline__ bool wq_is_nan(double q, double dx, double dy, double dz) {
+  return q != 0.0 && (dx != dx || dy != dy || dz != dz);
 }
 
-__device__ __forceinline__ double col_weight(double q, double x, double y, double z) {
-  return x != x || y != y || z != z ? x + y + z : q;
+__device__ __forceinline__ bool not_finite3(double x, double y, double z) {
+  return !(fabs(x) < __builtin_inf() && fabs(y) < __builtin_inf() && fabs(z) < __builtin_inf());
 }
 
 // W[i*npad + j] = w(|x_i - x_j|) q_j, FP64 arithmetic rounded once to FP32;
@@ -1118,11 +1121,14 @@ __global__ __launch_bounds__(kWG) void k_w_build_f32(const double* __restrict__ 
   const int64_t i0 = (int64_t)blockIdx.x * kWBuildRows;
   const int64_t j = (int64_t)blockIdx.y * kWG + threadIdx.x;   // npad is a multiple of kWG
   const double xj = xyz64[3 * j], yj = xyz64[3 * j + 1], zj = xyz64[3 * j + 2];
-  const double qj = qd[j] == 0.0 ? 0.0 : col_weight(qd[j], xj, yj, zj);
+  const double qj = qd[j];
+  const bool special = __any(not_finite3(xj, yj, zj));
   const int64_t i1 = i0 + kWBuildRows < n ? i0 + kWBuildRows : n;
   for (int64_t i = i0; i < i1; ++i) {
     const double xi = xyz64[3 * i], yi = xyz64[3 * i + 1], zi = xyz64[3 * i + 2];
-    W[i * npad + j] = (float)(kernel_w64<KIND>(kp, we, row_amp(kp.Ae, xi, yi, zi), xi - xj, yi - yj, zi - zj) * qj);
+    float wq = (float)kernel_wq64<KIND>(kp, we, qj, xi - xj, yi - yj, zi - zj);
+    if ((special || not_finite3(xi, yi, zi)) && wq_is_nan(qj, xi - xj, yi - yj, zi - zj)) wq = __builtin_nanf("");
+    W[i * npad + j] = wq;
   }
 }
 

@@ -138,13 +138,15 @@ __global__ __launch_bounds__(kWG) void k_mfma_w_build(const double* __restrict__
   }
   const double scale = ldexp(1.0, sW);
   double x[8], y[8], z[8], q[8];
+  bool special = false;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const int64_t j = 16 * kb + 8 * h + e;
     x[e] = xyz64[3 * j];
     y[e] = xyz64[3 * j + 1];
     z[e] = xyz64[3 * j + 2];
-    q[e] = qd[j] == 0.0 ? 0.0 : col_weight(qd[j], x[e], y[e], z[e]) * scale;
+    q[e] = qd[j] * scale;
+    special |= not_finite3(x[e], y[e], z[e]);
   }
   const int64_t ngroups = npad / kMfmaRowsPerWG;
   for (int64_t g = (int64_t)blockIdx.x * kWBuildGroups; g < ngroups && g < ((int64_t)blockIdx.x + 1) * kWBuildGroups; ++g) {
@@ -153,17 +155,24 @@ __global__ __launch_bounds__(kWG) void k_mfma_w_build(const double* __restrict__
     for (int r = 0; r < 4; ++r) {
       const int64_t i = g * kMfmaRowsPerWG + r * 32 + m;
       const double xi = xyz64[3 * i], yi = xyz64[3 * i + 1], zi = xyz64[3 * i + 2];
-      const double Ae = row_amp(kp.Ae, xi, yi, zi);
       T hi[8], lo[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e)
-        split_hi_lo<T>(kernel_w64<KIND>(kp, we, Ae, xi - x[e], yi - y[e], zi - z[e]) * q[e], hi[e], lo[e]);
+        split_hi_lo<T>(kernel_wq64<KIND>(kp, we, q[e], xi - x[e], yi - y[e], zi - z[e]), hi[e], lo[e]);
       u32x4_t vh, vl;
       __builtin_memcpy(&vh, hi, 16);
       __builtin_memcpy(&vl, lo, 16);
       if (i >= n) vh = vl = u32x4_t{0u, 0u, 0u, 0u};
       __builtin_nontemporal_store(vh, reinterpret_cast<u32x4_t*>(dst + r * 512));
       __builtin_nontemporal_store(vl, reinterpret_cast<u32x4_t*>(dst + (4 + r) * 512));
+      if (__any(special || not_finite3(xi, yi, zi))) {   // the entries that are NaN, one by one
+#pragma unroll 1
+        for (int e = 0; e < 8; ++e) {
+          const int64_t j = 16 * kb + 8 * h + e;
+          if (i >= n || !wq_is_nan(qd[j], xi - xyz64[3 * j], yi - xyz64[3 * j + 1], zi - xyz64[3 * j + 2])) continue;
+          dst[r * 512 + e] = dst[(4 + r) * 512 + e] = (T)__builtin_nanf("");
+        }
+      }
     }
   }
 }
