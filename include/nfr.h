@@ -285,7 +285,11 @@ int nfr_apply(nfr_problem* prob, const nfr_kernel* kernel, const nfr_firing* fir
  * array of NFR_APPLY_NOALLOC_MAX_BYTES inside the library, one per GPU,
  * held until the process ends.  An application whose
  * nfr_apply_workspace_size exceeds that size fails with NFR_ERR_WORKSPACE
- * before anything is enqueued.  The call allocates nothing (no hipMalloc, no
+ * before anything is enqueued; except ONTHEFLY_FP32 with several states, which
+ * then runs in groups of states, as long as npad B (4 + 8 s) is within it
+ * (npad the padded node count, s the partial sums per node and state that
+ * about 1024 workgroups of 512 targets x 16 states, 1024 x 16 up to 4 states,
+ * leave, or a tuned number of them).  The call allocates nothing (no hipMalloc, no
  * library allocation).  Every call on one GPU shares that GPU's array and the
  * kernels overwrite every scratch byte they read (nothing needs clearing), so
  * calls whose work overlaps on one GPU (other streams, other threads, other

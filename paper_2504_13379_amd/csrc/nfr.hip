@@ -252,9 +252,11 @@ constexpr int64_t kTargetWGs = 1024;   // about four workgroups per compute unit
 constexpr int64_t kGraphMaxSteps = 64;  // RK4 steps per captured graph of nfr_integrate
 constexpr int64_t kBatchGraphMaxSteps = 16;  // RK4 steps per captured graph of nfr_batch_integrate
 
+constexpr int64_t kComputeUnits = 256;
+
 struct OtfPlan {
   int bs = 1, nsb = 1, tpt = 1;
-  int64_t tiles = 0, chunk = 0;
+  int64_t tiles = 0, grain = 0, chunk = 0;
   int nsplit = 1;
 };
 
@@ -294,20 +296,8 @@ int64_t otf_target_wgs(int64_t npad, int B) {
   return best;
 }
 
-// Slots that a target of workgroups gives with blocks of 16 states on the vector
-// units (512 targets per workgroup, 1024 up to 4 states): the split of the
-// first version, whose workspace sizes bound the present plan's.
-int64_t otf_base_split(int64_t npad, int B, int64_t target) {
-  const int64_t tiles = ceil_div(npad, (int64_t)kWG * (B <= 4 ? 4 : 2)) * ceil_div(B, 16);
-  const int64_t want = std::min(std::max<int64_t>(ceil_div(target, tiles), 1), npad / kWG);
-  return ceil_div(npad, round_up(ceil_div(npad, want), kWG));
-}
-
-// Two workgroups per target of the tune table: with 2048 the last ones leave
-// less of the chip idle (N = 20011, 16 states: 282 against 296 us per
-// application; 7 states 224 / 238, 2 states 183 / 204).  More slots would let
-// nfr_apply_noalloc refuse a problem that it took before: then as before.
-OtfPlan plan_otf_target(int64_t npad, int B, int64_t target) {
+// Kernel shape of the multi-state sum, everything but its split into source chunks.
+OtfPlan otf_shape(int64_t npad, int B) {
   OtfPlan p;
   p.bs = otf_bs(B);
   p.nsb = (int)ceil_div(B, p.bs);
@@ -320,14 +310,56 @@ OtfPlan plan_otf_target(int64_t npad, int B, int64_t target) {
     while (p.tpt > 1 && p.bs > 1 && npad / (64 * p.tpt) * ceil_div(npad, 4 * kWG) * p.nsb < 512) p.tpt /= 2;
   }
   p.tiles = npad / (vec ? 64 * p.tpt : kWG);
-  const int64_t grain = vec ? 4 * kWG : kWG;
-  int64_t want = ceil_div(2 * target, p.tiles * p.nsb);
-  const int64_t slot = (int64_t)B * npad * 8, base = otf_base_split(npad, B, target);
-  const int64_t room = ((int64_t)NFR_APPLY_NOALLOC_MAX_BYTES - 512 - npad * B * 4) / slot;
-  if (base <= room && want > room) want = std::max(base, room);
-  if (want < 1) want = 1;
-  p.chunk = round_up(ceil_div(npad, want), grain);
-  p.nsplit = (int)ceil_div(npad, p.chunk);
+  p.grain = vec ? 4 * kWG : kWG;
+  return p;
+}
+
+// Time of one application split into chunks of `chunk` sources, in clocks.  The
+// busiest compute unit gets c workgroups, the last chunk's shorter ones last where
+// they make a layer of their own, R of them resident at once; r together take
+// r + a, a lone one hiding little of its own latency (least with one target per
+// lane), and the ends are not in step (0.1 R).  The combine then reads every slot
+// (3 TB/s).  The constants are from a sweep of 1 to 80 slots over N = 2000 to 65536
+// and 2 to 113 states.
+double otf_cost(const OtfPlan& p, int64_t npad, int B, int64_t chunk) {
+  const bool vec = p.bs <= 8;
+  const int nb = p.bs / 16;
+  const double clocks = vec ? 0.25 * p.tpt * (43.0 + 2.2 * p.bs) : 43.0 + 32.0 * nb;   // of a workgroup per source
+  const int R = vec ? 5 : (nb == 1 ? 4 : (nb == 2 ? 3 : 2));
+  const double a = vec ? (p.tpt == 4 ? 0.5 : (p.tpt == 2 ? 1.2 : 2.7)) : 0.5;
+  const int64_t slots = ceil_div(npad, chunk), wgs = p.tiles * p.nsb;
+  const int64_t full = ceil_div(wgs * (slots - 1), kComputeUnits), all = ceil_div(wgs * slots, kComputeUnits);
+  const double c = (double)full + (double)(all - full) * (double)(npad - (slots - 1) * chunk) / (double)chunk;
+  const double rounds = std::floor(c / R), rest = c - rounds * R;
+  const double items = rounds * (R + a) + rest + a * std::min(rest, 1.0) + 0.1 * R;
+  return items * (double)chunk * clocks + (double)slots * B * npad * 8.0 * (2.1e9 / 3e12);
+}
+
+// The split: of the slot counts up to six workgroups per target of the tune
+// table, 48 slots over the state blocks of the matrix cores (32 on the vector
+// units) and 256 MB of them, the last-level cache's size, the one of least cost:
+// 0.6 % slower than the best of the sweep on average, 12 % at most (7000 nodes, 12
+// states).  With two workgroups per target and the slots held below
+// nfr_apply_noalloc's size instead, N = 43776 with 50 states took 4.15 ms per
+// application, now 2.72, N = 33000 2.30, now 1.64; N = 9700 with 64 states 205 us
+// with 38 slots, now 170 with 13.  No more slots than let one state fit
+// nfr_apply_noalloc's scratch.
+OtfPlan plan_otf_target(int64_t npad, int B, int64_t target) {
+  OtfPlan p = otf_shape(npad, B);
+  const int64_t one_state = ((int64_t)kScratchBytes - npad * 4) / (npad * 8);
+  const int64_t cached = std::max<int64_t>((int64_t(256) << 20) / (npad * B * 8), 1);
+  const int64_t most = std::min({p.bs <= 8 ? int64_t(32) : std::max<int64_t>(48 / p.nsb, 1), cached, one_state});
+  const int64_t want = std::max<int64_t>(std::min(ceil_div(6 * target, p.tiles * p.nsb), most), 1);
+  auto chunk_of = [&](int64_t slots) { return round_up(ceil_div(npad, slots), p.grain); };
+  double least = 1e300;
+  for (int64_t slots = ceil_div(npad, chunk_of(want)); slots > 0;
+       slots = slots > 1 ? ceil_div(npad, chunk_of(slots - 1)) : 0) {
+    const double cost = otf_cost(p, npad, B, chunk_of(slots));
+    if (cost > least) continue;
+    least = cost;
+    p.chunk = chunk_of(slots);
+    p.nsplit = (int)slots;
+  }
   return p;
 }
 
@@ -388,7 +420,7 @@ int64_t adj_tiles(int64_t npad) { return ceil_div(npad, kSymTile); }
 #ifndef NFR_SYM_ALL_MAX
 #define NFR_SYM_ALL_MAX 64
 #endif
-constexpr int64_t kComputeUnits = 256, kSymRestMax = NFR_SYM_REST_MAX, kSymAllMax = NFR_SYM_ALL_MAX;
+constexpr int64_t kSymRestMax = NFR_SYM_REST_MAX, kSymAllMax = NFR_SYM_ALL_MAX;
 SymRest sym_rest_of(int64_t nt, bool all) {
   const int64_t pairs = sym_pairs(nt);
   int64_t rem = nt <= 128 ? pairs % kComputeUnits : 0;
@@ -473,6 +505,7 @@ struct Workspace {
   double* ksum = nullptr;
   double* ut = nullptr;        // fused BF16 form: states in the tile order (n x B)
   double* yt = nullptr;        // fused BF16 form, one application: the result in the tile order
+  bool sym = false;            // one state on the symmetric or the small kernel (use_sym)
   OtfPlan otf;                 // multi-state on-the-fly FP32 plan (unused by other forms)
   int nsplit = 1;              // partial-sum slots per node and state in `part`
   size_t bytes = 0;
@@ -495,7 +528,8 @@ Workspace carve(void* base, const ProblemView& pv, int B, int form, bool steppin
     off += align256(bytes);
     return r;
   };
-  if (form == NFR_FORM_ONTHEFLY_FP32 && !use_sym(form, B, pv.npad)) w.otf = plan_otf(pv.npad, B);
+  w.sym = use_sym(form, B, pv.npad);
+  if (form == NFR_FORM_ONTHEFLY_FP32 && !w.sym) w.otf = plan_otf(pv.npad, B);
   w.nsplit = nsplit_of(pv, B, form, w.otf);
   const size_t gbytes = is_mfma_form(form) ? mfma_g_bytes(pv.npad, B) : size_t(pv.npad) * B * sizeof(float);
   w.g = reinterpret_cast<float*>(take(gbytes));
@@ -590,7 +624,7 @@ int timing_mark(nfr_context* ctx) {
 int launch_pairs_raw(const ProblemView& pv, const nfr_kernel& k_in, int form, int B, const void* W, const Workspace& w,
                      hipStream_t s) {
   const nfr_kernel k = norm_kernel(k_in);
-  if (use_sym(form, B, pv.npad)) {
+  if (w.sym) {
     const PairParams pp = pair_params_pow(k, pv);
 #define NFR_SYM_CASE(K) \
   case K: launch_sym<K>(pv, pp, w.g, w.part, s); break;
@@ -1137,6 +1171,21 @@ int apply_check(const nfr_problem* prob, const nfr_kernel* kernel, const nfr_fir
   return check_w(prob, *form, w_dev);
 }
 
+// Whether nfr_apply_noalloc takes a several-state on-the-fly FP32 application:
+// its limit (nfr.h) counts the fewer of the slots of workgroups of 512 targets and
+// 16 states (1024 targets up to 4 states) at one per target of the tune table, and
+// of the kernel's own workgroups at two, whatever split the plan then takes.
+bool noalloc_takes(int64_t npad, int B) {
+  const OtfPlan p = otf_shape(npad, B);
+  const int64_t target = B == 1 ? kTargetWGs : otf_target_wgs(npad, B);
+  auto slots = [&](int64_t wgs, int64_t per_slot, int64_t grain) {
+    return ceil_div(npad, round_up(ceil_div(npad, std::min(ceil_div(wgs, per_slot), npad / kWG)), grain));
+  };
+  const int64_t s = std::min(slots(target, ceil_div(npad, (int64_t)kWG * (B <= 4 ? 4 : 2)) * ceil_div(B, 16), kWG),
+                             slots(2 * target, p.tiles * p.nsb, p.grain));
+  return npad * B * (4 + 8 * s) <= (int64_t)kScratchBytes;
+}
+
 // Prep, pair sums and reduction of one application into y_dev, with the
 // scratch of `w` (carved by the caller).
 int apply_launch(nfr_problem* prob, const nfr_kernel* kernel, const nfr_firing* firing, int B, const double* u_dev,
@@ -1155,7 +1204,7 @@ int apply_launch(nfr_problem* prob, const nfr_kernel* kernel, const nfr_firing* 
     y_out = w.yt;
   }
   if ((st = launch_prep(pv, form, B, u_in, fr, w, nullptr, s))) return st;
-  if (use_small_stage(pv, form, B)) {
+  if (w.sym && small_onesided(pv.npad)) {
     // the one-sided kernel's single slot is the result
     Workspace direct = w;
     direct.part = y_out;
@@ -1193,11 +1242,27 @@ int nfr_apply_noalloc(nfr_problem* prob, const nfr_kernel* kernel, const nfr_fir
   void* base = scratch_of(prob->ctx->device);
   if (!base) return fail(NFR_ERR_INTERNAL, "no scratch address for device %d", prob->ctx->device);
   // carved once (the plan is read once); nothing is launched unless it fits
-  const Workspace w = carve(base, prob->view, B, form, false);
-  if (w.bytes > kScratchBytes)
+  Workspace w = carve(base, prob->view, B, form, false);
+  const int64_t n = prob->view.n, npad = prob->view.npad;
+  const bool otf = form == NFR_FORM_ONTHEFLY_FP32 && !w.sym;
+  if (otf ? !noalloc_takes(npad, B) : w.bytes > kScratchBytes)
     return fail(NFR_ERR_WORKSPACE, "this application needs %zu scratch bytes; the fixed scratch holds %zu (use nfr_apply with a workspace)",
                 w.bytes, kScratchBytes);
-  return apply_launch(prob, kernel, firing, B, u_dev, y_dev, form, w_dev, w);
+  if (w.bytes <= kScratchBytes) return apply_launch(prob, kernel, firing, B, u_dev, y_dev, form, w_dev, w);
+  // groups of states under the whole call's plan: a state's sums do not depend on
+  // the states beside it, so the result is nfr_apply's bit for bit
+  const int group = (int)((int64_t)kScratchBytes / (npad * (4 + 8 * (int64_t)w.otf.nsplit)));
+  if (group < 1) return fail(NFR_ERR_INTERNAL, "a state does not fit the scratch");   // plan_otf_target keeps one fitting
+  for (int b0 = 0; b0 < B; b0 += group) {
+    const int m = std::min(group, B - b0);
+    w.otf.nsb = (int)ceil_div(m, w.otf.bs);
+    w.g = static_cast<float*>(base);
+    w.part = reinterpret_cast<double*>(static_cast<char*>(base) + align256(size_t(npad) * m * sizeof(float)));
+    nfr_firing fg = *firing;
+    if (fg.theta_dev) fg.theta_dev += b0;
+    if ((st = apply_launch(prob, kernel, &fg, m, u_dev + b0 * n, y_dev + b0 * n, form, w_dev, w))) return st;
+  }
+  return NFR_OK;
 }
 
 size_t nfr_integrate_workspace_size(const nfr_problem* prob, int B, int form) {
