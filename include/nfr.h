@@ -425,8 +425,9 @@ size_t nfr_tune_workspace_size(int64_t n_max, int B_max);
 /* Times the candidate workgroup targets (256 ... 4096) of the multi-state pair
  * sum on synthetic problems (spherical Fibonacci nodes, n = n_max/16, n_max/4,
  * n_max, at least 1024; B = 2, 4, 16, 64, 256 up to B_max; Gaussian Mexican
- * hat), installs the fastest per (n, B) in the process-wide table and, if
- * cache_path is non-NULL, writes them there as JSON.  1024 <= n_max <= 4e6,
+ * hat), installs the fastest per (n, B) in the process-wide table (the built-in
+ * target, which is among those timed, where none is faster) and, if
+ * cache_path is non-NULL, writes them there as JSON with both times.  1024 <= n_max <= 4e6,
  * 2 <= B_max.  Synchronous. */
 int nfr_tune(nfr_context* ctx, const char* cache_path, int64_t n_max, int B_max, void* ws_dev, size_t ws_bytes);
 /* Installs the entries of a cache written by nfr_tune (host only). */

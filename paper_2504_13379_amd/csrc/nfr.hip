@@ -2301,7 +2301,6 @@ namespace {
 
 constexpr int kTuneB[] = {2, 4, 16, 64, 256};
 constexpr int64_t kTuneTargets[] = {256, 512, 1024, 2048, 4096};
-constexpr int kTuneMaxSplit = 16;
 
 std::vector<int64_t> tune_sizes(int64_t n_max) {
   std::vector<int64_t> out;
@@ -2316,6 +2315,7 @@ struct TuneLayout {
   size_t xyz = 0, q = 0, pack = 0, g = 0, part = 0, bytes = 0;
 };
 
+// `part` holds the partial sums of every plan that nfr_tune times.
 TuneLayout tune_layout(int64_t n_max, int B_max) {
   TuneLayout L;
   const int64_t npad = round_up(n_max, kPad);
@@ -2330,7 +2330,15 @@ TuneLayout tune_layout(int64_t n_max, int B_max) {
   L.g = off;
   off += align256(size_t(npad) * Bm * sizeof(float));
   L.part = off;
-  off += align256(size_t(kTuneMaxSplit) * Bm * npad * sizeof(double));
+  size_t part = 0;
+  for (int64_t n : tune_sizes(n_max))
+    for (int B : kTuneB)
+      for (int64_t target : kTuneTargets) {
+        if (B > B_max) continue;
+        const int64_t np = round_up(n, kPad);
+        part = std::max(part, size_t(plan_otf_target(np, B, target).nsplit) * B * np * sizeof(double));
+      }
+  off += align256(part);
   L.bytes = off;
   return L;
 }
@@ -2410,7 +2418,7 @@ int nfr_tune(nfr_context* ctx, const char* cache_path, int64_t n_max, int B_max,
   } events{ev0, ev1};
   const nfr_kernel kern{NFR_KERNEL_GAUSS_MH, 1.0, 0.15, 0.5, 0.4};
   std::vector<TuneEntry> found;
-  std::vector<double> found_ms;
+  std::vector<double> found_ms, untuned_ms_of;   // of the chosen target, of the untuned one
   for (int64_t n : tune_sizes(n_max)) {
     // a synthetic surface: spherical Fibonacci nodes, equal weights
     std::vector<double> xyz(size_t(3) * n), q(size_t(n), 4.0 * M_PI / (double)n);
@@ -2439,27 +2447,34 @@ int nfr_tune(nfr_context* ctx, const char* cache_path, int64_t n_max, int B_max,
       if (B > B_max) break;
       NFR_HIP(hipMemsetAsync(g, 0, size_t(pv.npad) * B * sizeof(float), s));
       int64_t best_t = kTargetWGs;
-      double best_ms = 1e300;
-      int64_t last_split = -1;
+      double best_ms = 1e300, untuned_ms = 0.0;
+      int64_t last_split = -1, best_split = -1;
+      float ms = 0.0f;
       for (int64_t target : kTuneTargets) {
         const OtfPlan pl = plan_otf_target(pv.npad, B, target);
-        if ((int64_t)pl.nsplit * B > (int64_t)kTuneMaxSplit * std::min(B_max, 256) || pl.nsplit == last_split) continue;   // same launch as the previous target
-        last_split = pl.nsplit;
-        launch_otf_kind<0>(pv, pp, B, g, part, pl, s);
-        NFR_HIP(hipEventRecord(ev0, s));
-        for (int r = 0; r < 3; ++r) launch_otf_kind<0>(pv, pp, B, g, part, pl, s);
-        NFR_HIP(hipEventRecord(ev1, s));
-        NFR_HIP_LAUNCH();
-        NFR_HIP(hipEventSynchronize(ev1));
-        float ms = 0.0f;
-        NFR_HIP(hipEventElapsedTime(&ms, ev0, ev1));
-        if (ms / 3.0 < best_ms) {
-          best_ms = ms / 3.0;
-          best_t = target;
+        if (pl.nsplit != last_split) {   // else the same launch as the previous target's
+          last_split = pl.nsplit;
+          launch_otf_kind<0>(pv, pp, B, g, part, pl, s);
+          NFR_HIP(hipEventRecord(ev0, s));
+          for (int r = 0; r < 3; ++r) launch_otf_kind<0>(pv, pp, B, g, part, pl, s);
+          NFR_HIP(hipEventRecord(ev1, s));
+          NFR_HIP_LAUNCH();
+          NFR_HIP(hipEventSynchronize(ev1));
+          NFR_HIP(hipEventElapsedTime(&ms, ev0, ev1));
+          if (ms / 3.0 < best_ms) {
+            best_ms = ms / 3.0;
+            best_t = target;
+            best_split = pl.nsplit;
+          }
+        }
+        if (target == kTargetWGs) {
+          untuned_ms = ms / 3.0;
+          if (pl.nsplit == best_split) best_t = target;   // a bound that changed nothing stays away from the sizes around
         }
       }
       found.push_back(TuneEntry{pv.npad, B, best_t});
       found_ms.push_back(best_ms);
+      untuned_ms_of.push_back(untuned_ms);
     }
   }
   tune_install(found);
@@ -2468,8 +2483,9 @@ int nfr_tune(nfr_context* ctx, const char* cache_path, int64_t n_max, int B_max,
     if (!f) return fail(NFR_ERR_INVALID_ARG, "cannot write %s", cache_path);
     std::fprintf(f, "{\"library\": \"nfr\", \"arch\": \"%s\", \"tuned\": \"multi-state on-the-fly pair sum, workgroup target\",\n \"entries\": [\n", ctx->arch);
     for (size_t i = 0; i < found.size(); ++i)
-      std::fprintf(f, "  {\"npad\": %lld, \"B\": %d, \"target_wgs\": %lld, \"ms\": %.6f}%s\n", (long long)found[i].npad,
-                   found[i].B, (long long)found[i].target, found_ms[i], i + 1 < found.size() ? "," : "");
+      std::fprintf(f, "  {\"npad\": %lld, \"B\": %d, \"target_wgs\": %lld, \"ms\": %.6f, \"untuned_ms\": %.6f}%s\n",
+                   (long long)found[i].npad, found[i].B, (long long)found[i].target, found_ms[i], untuned_ms_of[i],
+                   i + 1 < found.size() ? "," : "");
     std::fprintf(f, " ]\n}\n");
     if (std::fclose(f) != 0) return fail(NFR_ERR_INVALID_ARG, "cannot write %s", cache_path);
   }
