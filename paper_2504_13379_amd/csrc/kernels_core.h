@@ -643,8 +643,8 @@ __device__ inline void sym_group(const float4* __restrict__ src, const float* __
 
 // part[s * npad + i]: slot s of node i (see above); nt = ceil(npad / (64 TPT)).
 // Workgroups below `whole` take a tile pair each; the four groups of every later
-// pair (rem pairs, the last of the order, fewer than two rows of it) take a
-// workgroup each.  Group 0's row sums go to slot J, group k's to the extra slot
+// pair (the last of the order, in up to five rows of it; the transpose kernel splits
+// all pairs of up to 10 tiles) take a workgroup each.  Group 0's row sums go to slot J, group k's to the extra slot
 // nt + 3 (nt - 1 - J) + k - 1; the diagonal pairs clear the extra slots that no
 // group of their tile writes.
 template <int KIND, int TPT, int SPLIT, int UNROLL>
