@@ -97,11 +97,13 @@ __global__ __launch_bounds__(kGridThreads) void k_quad_grid(const double* __rest
   double ext[3], emax = 0.0;
   for (int d = 0; d < 3; ++d) {
     ext[d] = s_hi[d][0] - s_lo[d][0];
+    if (!(ext[d] < __builtin_inf())) ext[d] = 0.0;   // not finite: one layer of cells, as the search below ends for any
     emax = fmax(emax, ext[d]);
   }
   if (!(emax > 0.0)) emax = 1.0;
   // volume, with flat directions given a thousandth of the largest extent
   double h = cbrt(fmax(ext[0], emax * 1e-3) * fmax(ext[1], emax * 1e-3) * fmax(ext[2], emax * 1e-3) * 4.0 / (double)n);
+  if (!(h > 0.0 && h < __builtin_inf())) h = emax;   // a volume beyond FP64's range: at most 8 cells
   int dim[3];
   for (;;) {
     int64_t cells = 1;
@@ -123,7 +125,7 @@ __global__ __launch_bounds__(kGridThreads) void k_quad_grid(const double* __rest
 
 __device__ inline int quad_cell_coord(double x, double o, double h, int dim) {
   const double c = floor((x - o) / h);
-  return c < 0.0 ? 0 : (c >= (double)dim ? dim - 1 : (int)c);
+  return !(c > 0.0) ? 0 : (c >= (double)dim ? dim - 1 : (int)c);   // NaN: 0
 }
 
 __device__ inline int64_t quad_cell_of(const QuadGrid& g, double x, double y, double z) {
