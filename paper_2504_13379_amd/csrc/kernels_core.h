@@ -461,9 +461,11 @@ __device__ __forceinline__ void put_sources(float4* srcs, int lane, float4 v) {
 // the scheduler spreads them and loses that (N = 65536, Gaussian: 618 us per
 // launch with 1, 747 with 2, 750 with 4; exponential 606 / 736 / 690; forcing an
 // exponential every five instructions 15 % slower than 4).
-// Where a compute unit has at most two workgroups, their few waves hide less of
-// their own latency and four steps are better (N = 6914: 22.8 against 23.2 us per
-// stage).
+// Where a compute unit has at most two workgroups and they end together (no pair
+// is split: 28 to 31 tiles), their few waves hide less of their own latency and
+// four steps are better: per stage 21.0 us against 22.8 at N = 7200 and 7900; with
+// split pairs 21.0 / 20.2 at N = 6300, 21.7 / 20.9 at 6912 (27 tiles); beyond two
+// workgroups 24.9 / 23.8 at N = 8200, 31.4 / 28.7 at 10000.
 
 template <int KIND, bool COLS, int TPT, int SPLIT, int UNROLL>
 __device__ inline void sym_tile(const float4* __restrict__ src, const float* __restrict__ g, int64_t npad,

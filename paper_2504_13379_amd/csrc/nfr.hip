@@ -461,7 +461,7 @@ void launch_sym(const ProblemView& pv, const PairParams& pp, const float* g, dou
   } else {
     const SymRest rest = sym_rest(pv.npad);
     const dim3 grid((unsigned)(rest.whole + 4 * (pairs - rest.whole)));
-    if (pairs <= 2 * kComputeUnits)
+    if (pairs <= 2 * kComputeUnits && rest.rows == 0)   // four rotation steps per iteration (see sym_tile)
       hipLaunchKernelGGL((k_otf_sym<K, kSymTPT, kSymSplit, 4>), grid, dim3(kSymThreads), 0, s, pv.src, g, pv.npad, pp,
                          rest, part);
     else
