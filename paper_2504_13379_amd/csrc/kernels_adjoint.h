@@ -34,17 +34,13 @@ namespace nfr {
 // Waves per workgroup of the transpose kernel (they split a tile's source
 // groups like the forward kernel's; one group per wave measured fastest at
 // N = 16384: 1, 2, 4 waves took 0.089, 0.082, 0.077 ms per pair launch).
-#ifndef NFR_ADJ_SPLIT
-#define NFR_ADJ_SPLIT 4
-#endif
-constexpr int kAdjSplit = NFR_ADJ_SPLIT;
+constexpr int kAdjSplit = 4;               // sym_adj_group: a wave per channel
 constexpr int kAdjThreads = 64 * kAdjSplit;
 
 template <int KIND, bool COLS, int UNROLL>
 __device__ inline void sym_adj_tile(const float4* __restrict__ src, const float* __restrict__ lam, int64_t npad,
                                     int nslots, const PairParams& pp, double* __restrict__ part, int64_t I, int64_t J,
                                     double (*rowsum)[4][kSymTile], float4 (*srcs)[128]) {
-  static_assert(kSymTile == 64 * kSymTPT, "one wave holds the tile's targets");
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const float rho = pp.rho;
@@ -118,30 +114,20 @@ __device__ inline void sym_adj_tile(const float4* __restrict__ src, const float*
       for (int c = 0; c < 4; ++c) part[((int64_t)c * nslots + I) * npad + j] = (double)col[c];
     }
   }
-  if (kAdjSplit > 1) {
 #pragma unroll
-    for (int k = 0; k < kSymTPT; ++k)
+  for (int k = 0; k < kSymTPT; ++k)
 #pragma unroll
-      for (int c = 0; c < 4; ++c) rowsum[wave][c][k * 64 + lane] = racc[k][c];
-    __syncthreads();
-    for (int tt = threadIdx.x; tt < kSymTile; tt += kAdjThreads) {
-      const int64_t t = I * kSymTile + tt;
-      if (t >= npad) continue;
+    for (int c = 0; c < 4; ++c) rowsum[wave][c][k * 64 + lane] = racc[k][c];
+  __syncthreads();
+  for (int tt = threadIdx.x; tt < kSymTile; tt += kAdjThreads) {
+    const int64_t t = I * kSymTile + tt;
+    if (t >= npad) continue;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        double sum = 0.0;
+    for (int c = 0; c < 4; ++c) {
+      double sum = 0.0;
 #pragma unroll
-        for (int w = 0; w < kAdjSplit; ++w) sum += rowsum[w][c][tt];
-        part[((int64_t)c * nslots + J) * npad + t] = sum;
-      }
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < kSymTPT; ++k) {
-      const int64_t t = I * kSymTile + k * 64 + lane;
-      if (t >= npad) continue;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) part[((int64_t)c * nslots + J) * npad + t] = racc[k][c];
+      for (int w = 0; w < kAdjSplit; ++w) sum += rowsum[w][c][tt];
+      part[((int64_t)c * nslots + J) * npad + t] = sum;
     }
   }
 }
@@ -157,7 +143,6 @@ __device__ inline void sym_adj_group(const float4* __restrict__ src, const float
                                      int grp, int64_t slot, float4* srcs, float (*val)[kAdjRound][kSymTPT][64]) {
   // sym_adj_tile's coordinates are rounded before they meet in the differences
 #pragma clang fp contract(off)
-  static_assert(kAdjSplit == 4, "a wave per channel");
   constexpr int TPT = kSymTPT, STEPS = kAdjRound / kAdjSplit;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

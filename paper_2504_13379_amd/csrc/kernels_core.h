@@ -393,16 +393,13 @@ __global__ __launch_bounds__(kWG) void k_otf_pair_sum(const float4* __restrict__
 // over all the tile's targets and the source is back in its lane.  Row sums:
 // FP32 per group of 64 sources, folded into FP64, then added over the waves
 // in wave order through LDS; column sums: FP32 over the wave, complete.
-#ifndef NFR_SYM_SPLIT
-#define NFR_SYM_SPLIT 4
-#endif
-#ifndef NFR_SYM_TPT
-#define NFR_SYM_TPT 4
-#endif
-constexpr int kSymSplit = NFR_SYM_SPLIT;
-constexpr int kSymTPT = NFR_SYM_TPT;
+// Both are fixed at 4: a split pair's groups are as many as the waves, and a thread
+// of the workgroup clears one node of the tile (sym_clear_rest).
+constexpr int kSymSplit = 4;
+constexpr int kSymTPT = 4;
 constexpr int kSymThreads = 64 * kSymSplit;
-constexpr int kSymTile = 64 * kSymTPT;   // 256 nodes by default
+constexpr int kSymTile = 64 * kSymTPT;
+static_assert(kSymThreads == kSymTile, "a thread per node of a tile");
 // Shape for small problems: one wave per tile pair and one target per lane
 // (tiles of 64), so that a few thousand nodes still give hundreds of tile
 // pairs; the large shape's 4-target tiles leave most of the chip idle there.
