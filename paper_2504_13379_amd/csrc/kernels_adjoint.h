@@ -23,17 +23,16 @@ namespace nfr {
 // Symmetric transpose sum: every term of S1, S2, T1, T2 is symmetric in
 // (i, j), so the tile-pair scheme of the forward symmetric kernel applies
 // (kernels_core.h: tile pairs I <= J, the targets of tile I held kSymTPT per lane,
-// source groups of J split over the waves, sources rotated by DPP carrying
-// their column accumulators), here with four channels weighted by lambda.
+// source groups of J split over the waves, sources read rotated from LDS, their
+// column accumulators following by DPP), here with four channels weighted by lambda.
 // Slots: part[(c * nslots + s) * npad + i] for channel c, slot s (the row sums of
 // (I, J) go to slot J of the nodes of I, the column sums to slot I of the
-// nodes of J).  The coordinates are in the forward kernel's units (t the
+// nodes of J, a split pair's further groups to extra slots as in k_otf_sym).  The coordinates are in the forward kernel's units (t the
 // excitatory argument); with rho = 1/m they are in units of the inhibitory
 // length instead, t the inhibitory argument, e2 = exp2(-t) and e1 = e2^m, and
 // the T channels hold sum lambda e t_i = T / m.
 // Waves per workgroup of the transpose kernel (they split a tile's source
-// groups like the forward kernel's; one group per wave measured fastest at
-// N = 16384: 1, 2, 4 waves took 0.089, 0.082, 0.077 ms per pair launch).
+// groups like the forward kernel's, a group each).
 constexpr int kAdjSplit = 4;               // sym_adj_group: a wave per channel
 constexpr int kAdjThreads = 64 * kAdjSplit;
 
@@ -209,7 +208,9 @@ __device__ inline void sym_adj_group(const float4* __restrict__ src, const float
 // each, the groups of the later ones a workgroup each, with the slots of
 // k_otf_sym: nslots = nt + 3 rest.rows per channel, nt = npad / kSymTile.  UNROLL:
 // rotation steps per iteration, 1 as in k_otf_sym (N = 16384: 93 -> 76 us per
-// launch) or, where a few waves must hide their own latencies, more.
+// launch) or, where a compute unit has one workgroup and few waves must hide their
+// own latencies, 4 (gradients with the kernel of length ratio 3 15 % faster at N =
+// 2600 to 4500, the Gaussian's the same; 13 % and 19 % slower at N = 16384).
 template <int KIND, int UNROLL>
 __global__ __launch_bounds__(kAdjThreads) void k_sym_adjoint(const float4* __restrict__ src,
                                                              const float* __restrict__ lam, int64_t npad,

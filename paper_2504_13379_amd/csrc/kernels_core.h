@@ -278,11 +278,13 @@ __device__ inline void otf_tile(const float4* __restrict__ src, const float* __r
 // states of the block; 64 pairs cost the matrix cores 32 clocks per 16 states,
 // where 16 vector multiply-adds take about 48, and the g values reach a wave
 // by one LDS read per four sources and 16 states instead of 16 broadcasts per
-// source.  Bound by vector issue and the FP32 matrix cores taking turns (about 43
-// clocks to evaluate 64 pairs, 32 per 16 states).  Per application with 16 / 32 /
-// 64 states: N = 20011 375 / 719 / 1488 -> 282 / 392 / 684 us, N = 65536 with 64
-// states 12.4 -> 5.9 ms; at 7 states the 8-state vector form takes 224 us, so the
-// matrix cores start at 9.
+// source.  Bound by vector issue and the FP32 matrix cores taking turns: the
+// counters show the matrix cores 61 % busy with 64 states (N = 65536), 32 % with 16
+// (N = 20011), never beside vector work, so 64 pairs take 32 clocks per 16 states and
+// 70 to 80 for their evaluation and its waits.  Per application with 16 / 32 /
+// 64 states: N = 20011 375 / 719 / 1488 -> 264 / 383 / 654 us, N = 65536 with 64
+// states 12.4 -> 5.9 ms; at 7 states the 8-state vector form takes 200 us (N =
+// 20011) and with 9 this one 258, the vector form in blocks of 16 states 360.
 // Output element r of lane l: target 16 (r / 4) + 4 (l / 16) + r % 4 of the
 // wave, state l % 16.
 typedef float f32x16v __attribute__((ext_vector_type(16)));
@@ -381,16 +383,18 @@ __global__ __launch_bounds__(kWG) void k_otf_pair_sum(const float4* __restrict__
 // Off-diagonal pairs (I < J) produce the row sums of tile I over sources in J
 // and the column sums of tile J over sources in I; diagonal pairs only row sums.
 // Slots: the row sums of (I, J) go to slot J of the nodes of I, the column
-// sums to slot I of the nodes of J, so every node receives exactly one
-// contribution per tile index and the combine adds slots 0..nt-1 in order.
+// sums to slot I of the nodes of J, so every node receives one contribution per
+// tile index; a pair split into its four groups leaves three more, in extra slots
+// behind these (k_otf_sym).  The combine adds all slots.
 //
 // Each lane keeps kSymTPT targets in registers, so one wave holds the whole
 // tile of 64 * kSymTPT targets; the kSymSplit waves of a workgroup share those
 // targets and split the tile's source groups between them (group g goes to
-// wave g mod kSymSplit).  A group of 64 sources is loaded one per lane and
-// rotated around the wave 64 times (DPP wave rotate by one lane); each source
-// carries its own column accumulators, so after a full turn they hold the sum
-// over all the tile's targets and the source is back in its lane.  Row sums:
+// wave g mod kSymSplit).  A group of 64 sources sits in LDS (put_sources), from
+// where lane l reads source (l - s) mod 64 at step s; the sources' column
+// accumulators follow by a DPP rotation of the wave by one lane per step, so after
+// 64 steps they hold the sum over all the tile's targets and are back in their
+// source's lane.  Row sums:
 // FP32 per group of 64 sources, folded into FP64, then added over the waves
 // in wave order through LDS; column sums: FP32 over the wave, complete.
 // Both are fixed at 4: a split pair's groups are as many as the waves, and a thread
@@ -453,11 +457,12 @@ __device__ __forceinline__ void put_sources(float4* srcs, int lane, float4 v) {
   __builtin_amdgcn_wave_barrier();
 }
 // Steps per iteration of the rotation loops: one.  Its 49 instructions keep each
-// step's eight exponentials together and the waves out of step, and the vector
-// units issue 1.9 clocks per plain instruction beside them; with 2 or 4 steps
-// the scheduler spreads them and loses that (N = 65536, Gaussian: 618 us per
-// launch with 1, 747 with 2, 750 with 4; exponential 606 / 736 / 690; forcing an
-// exponential every five instructions 15 % slower than 4).
+// step's eight exponentials together and the waves out of step, so that plain
+// instructions issue beside them: 18.7 lanes per clock and SIMD at N = 65538, 29 %
+// dual-issued (15.3 and 17 % with four steps and the sources rotated in registers).
+// With 2 or 4 steps the scheduler spreads them and loses that (N = 65536, Gaussian:
+// 618 us per launch with 1, 747 with 2, 750 with 4; exponential 606 / 736 / 690;
+// forcing an exponential every five instructions 15 % slower than 4).
 // Where a compute unit has at most two workgroups and they end together (no pair
 // is split: 28 to 31 tiles), their few waves hide less of their own latency and
 // four steps are better: per stage 21.0 us against 22.8 at N = 7200 and 7900; with

@@ -386,8 +386,13 @@ GemvPlan plan_gemv(int64_t n, int64_t npad, int B) {
 }
 
 // AUTO: FP32-class accuracy with no W matrix.  From 17 states on the FP32
-// matrix-core form (32 or 64 states per kernel value; at N = 65536, B = 64
-// 5.1 against 12.3 ms per application); below, the vector-unit sum.
+// matrix-core form, which takes states in blocks of 32 or 64; below, the default
+// form, in blocks of 16.  Per application at N = 65536, default / matrix-core form:
+// 16 states 2.46 / 3.18 ms, 17 3.30 / 3.19, 32 3.34 / 3.20, 33 4.60 / 5.11, 48 4.66 /
+// 5.15, 50 5.84 / 5.15, 64 5.91 / 5.18, 80 9.17 / 10.2, 128 11.8 / 10.3; at 33 to 48
+// and 65 to 96 states, which blocks of 64 pad, the default form asked for by name is
+// 7 to 17 % faster.  N = 2000 with 17 to 128 states: the matrix-core form 1.4 to 1.8
+// times as fast.
 int resolve_form(int form, int64_t n, int B) {
   if (form != NFR_FORM_AUTO) return form;
   (void)n;
@@ -2279,7 +2284,10 @@ int nfr_quad_weights(nfr_context* ctx, int64_t n, const double* xyz_dev, const d
   hipLaunchKernelGGL(k_scan_blocks, dim3((unsigned)nb), dim3(kWG), 0, s, w.cnt, n, w.bsum);
   hipLaunchKernelGGL(k_scan_totals, dim3(1), dim3(kWG), 0, s, w.bsum, nb);
   hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb), dim3(kWG), 0, s, w.cnt, n, w.bsum, w.off);
-  // registers for the smallest of four sizes that holds k (32 is the default stencil)
+  // registers for the smallest of four sizes that holds k: four equal steps of 12 to 13
+  // columns up to the largest, each about 700 more unrolled multiply-adds (N = 65538,
+  // whole call: k = 12 1.68 ms, 20 1.88, 21 2.22, 32 2.61, 33 3.14, 45 3.55, 46 4.57,
+  // 57 4.92; with the matrix in LDS 2.44, 3.37, 3.49, 6.53, 7.21, 13.9, 14.2, 29.6)
 #define NFR_QUAD_ELEMENTS(KP)                                                                                     \
   hipLaunchKernelGGL(k_quad_elements<KP>, dim3((unsigned)ntri), dim3(64), 0, s, xyz_dev, nrm_dev, w.tri, w.cen, \
                      w.nrm_tri, proj, stn, n, ntri, k, w.off, w.rank, w.val, w.list)
