@@ -27,10 +27,10 @@ namespace nfr {
 // column accumulators following by DPP), here with four channels weighted by lambda.
 // Slots: part[(c * nslots + s) * npad + i] for channel c, slot s (the row sums of
 // (I, J) go to slot J of the nodes of I, the column sums to slot I of the
-// nodes of J, a split pair's further groups to extra slots as in k_otf_sym).  The coordinates are in the forward kernel's units (t the
-// excitatory argument); with rho = 1/m they are in units of the inhibitory
-// length instead, t the inhibitory argument, e2 = exp2(-t) and e1 = e2^m, and
-// the T channels hold sum lambda e t_i = T / m.
+// nodes of J, a split pair's further groups to extra slots as in k_otf_sym).  The
+// coordinates are in the forward kernel's units (t the excitatory argument); with
+// rho = 1/m they are in units of the inhibitory length instead, t the inhibitory
+// argument, e2 = exp2(-t) and e1 = e2^m, and the T channels hold sum lambda e t_i = T / m.
 // Waves per workgroup of the transpose kernel (they split a tile's source
 // groups like the forward kernel's, a group each).
 constexpr int kAdjSplit = 4;               // sym_adj_group: a wave per channel
