@@ -2456,7 +2456,7 @@ int nfr_tune(nfr_context* ctx, const char* cache_path, int64_t n_max, int B_max,
       NFR_HIP(hipMemsetAsync(g, 0, size_t(pv.npad) * B * sizeof(float), s));
       int64_t best_t = kTargetWGs;
       double best_ms = 1e300, untuned_ms = 0.0;
-      int64_t last_split = -1, best_split = -1;
+      int64_t last_split = -1;
       float ms = 0.0f;
       for (int64_t target : kTuneTargets) {
         const OtfPlan pl = plan_otf_target(pv.npad, B, target);
@@ -2472,12 +2472,11 @@ int nfr_tune(nfr_context* ctx, const char* cache_path, int64_t n_max, int B_max,
           if (ms / 3.0 < best_ms) {
             best_ms = ms / 3.0;
             best_t = target;
-            best_split = pl.nsplit;
           }
         }
         if (target == kTargetWGs) {
           untuned_ms = ms / 3.0;
-          if (pl.nsplit == best_split) best_t = target;   // a bound that changed nothing stays away from the sizes around
+          if (untuned_ms <= best_ms) best_t = target;   // a bound that gained nothing stays away from the sizes around
         }
       }
       found.push_back(TuneEntry{pv.npad, B, best_t});
